@@ -62,7 +62,9 @@ __global__ void batch_reset_kernel(BatchHeader *hdr) {
 // LDS of the persistent kernel whose largest tile is MAXS.
 template <typename T, bool PRED, int MAXS>
 constexpr int batch_smem_bytes() {
-    return product_smem_bytes<T, MAXS, 16, PRED>();
+    const int p = product_smem_bytes<T, MAXS, 16, PRED>();
+    const int c = closure_smem_bytes<T, MAXS, false>();
+    return p > c ? p : c;
 }
 
 template <typename T, int S, int TMC, int TM, bool VEC, bool PRED>
@@ -244,7 +246,12 @@ __global__ void __launch_bounds__((staged_threads<T, S, PRED>()), (staged_waves<
 staged_kernel(const BatchItem *items, const StagedWork *work, int kind, int b) {
     constexpr int BK = staged_bk<T, S, PRED>();
     constexpr int NT = staged_threads<T, S, PRED>();
-    __shared__ __align__(16) char smem[product_smem_bytes<T, S, BK, PRED>()];
+    constexpr int kProduct = product_smem_bytes<T, S, BK, PRED>();
+    constexpr int kClosure = closure_smem_bytes<T, S, PRED>() > closure_smem_bytes<T, S, false>()
+                                 ? closure_smem_bytes<T, S, PRED>()
+                                 : closure_smem_bytes<T, S, false>();
+    constexpr bool kRoom = staged_can_close<T, S, PRED>() && kClosure > kProduct;
+    __shared__ __align__(16) char smem[kRoom ? kClosure : kProduct];
     const StagedWork w = work[blockIdx.x];
     const BatchItem it = items[w.item];
     if (kind == kStagedPredInit || kind == kStagedPredFix) {
@@ -280,9 +287,6 @@ staged_kernel(const BatchItem *items, const StagedWork *work, int kind, int b) {
             staged_product<T, S, BK, TM, TN, false, false>(it, kind, b, local, smem);
     }
     if constexpr (staged_can_close<T, S, PRED>()) {
-        static_assert(product_smem_bytes<T, S, BK, PRED>() >= closure_smem_bytes<T, S, PRED>() &&
-                          product_smem_bytes<T, S, BK, PRED>() >= closure_smem_bytes<T, S, false>(),
-                      "closure scratch must fit the product's LDS");
         if (w.local & kStagedClose) {
             __syncthreads();  // the tile's stores before its reloads
             T *d = as_global(static_cast<T *>(it.d));
@@ -301,26 +305,24 @@ constexpr bool staged_can_close() {
     return staged_tm<T, S, PRED>() == staged_tn<T, S, PRED>() && (S <= 64 || PRED);
 }
 
-// Diagonal tiles of stage b of many graphs: (S / TMC)^2 threads, the
-// geometry of the single-graph phase-1 kernel.
-template <int S>
-constexpr int staged_diag_tm() {
-    return S == 32 ? 2 : 4;
-}
+// Diagonal tiles of stage b of many graphs, in the geometry of the
+// single-graph phase-1 kernel (a plan with predecessors may hold graphs
+// without: both forms then share the predecessor form's geometry).
 template <typename T, int S, bool PRED>
-__global__ void __launch_bounds__((S / staged_diag_tm<S>()) * (S / staged_diag_tm<S>()))
+__global__ void __launch_bounds__((closure_threads<T, S, PRED, Ar<T>, false>()))
 staged_diag_kernel(const BatchItem *items, const StagedWork *work, int b) {
-    // a plan with predecessors may hold graphs without: room for both forms
     constexpr int kSmem = closure_smem_bytes<T, S, PRED>() > closure_smem_bytes<T, S, false>()
                               ? closure_smem_bytes<T, S, PRED>()
                               : closure_smem_bytes<T, S, false>();
+    constexpr int TM = closure_tm<T, S, PRED, Ar<T>, false>();
+    constexpr int TN = closure_tn<T, S, PRED, Ar<T>, false>();
     __shared__ __align__(16) char smem[kSmem];
     const BatchItem it = items[work[blockIdx.x].item];
     T *d = as_global(static_cast<T *>(it.d));
     if (PRED && it.p != nullptr)
-        closure_tile<T, S, staged_diag_tm<S>(), PRED>(d, as_global(it.p), it.n, it.ld, it.ldp, b * S, smem);
+        closure_tile<T, S, TM, PRED>(d, as_global(it.p), it.n, it.ld, it.ldp, b * S, smem);
     else
-        closure_tile_any<T, S, staged_diag_tm<S>(), false>(d, nullptr, it.n, it.ld, 0, b * S, smem);
+        closure_tile_any<T, S, TM, false, Ar<T>, TN>(d, nullptr, it.n, it.ld, 0, b * S, smem);
 }
 
 // ---------------------------------------------------------------------------
@@ -534,9 +536,9 @@ hipError_t launch_staged_t(int tile, const BatchItem *items, const StagedWork *w
     }
     if (kind == kStagedDiag) {
         switch (tile) {
-        case 32: staged_diag_kernel<T, 32, PRED><<<grid, 256, 0, st>>>(items, work, b); break;
-        case 64: staged_diag_kernel<T, 64, PRED><<<grid, 256, 0, st>>>(items, work, b); break;
-        case 128: staged_diag_kernel<T, 128, PRED><<<grid, 1024, 0, st>>>(items, work, b); break;
+        case 32: staged_diag_kernel<T, 32, PRED><<<grid, closure_threads<T, 32, PRED, Ar<T>, false>(), 0, st>>>(items, work, b); break;
+        case 64: staged_diag_kernel<T, 64, PRED><<<grid, closure_threads<T, 64, PRED, Ar<T>, false>(), 0, st>>>(items, work, b); break;
+        case 128: staged_diag_kernel<T, 128, PRED><<<grid, closure_threads<T, 128, PRED, Ar<T>, false>(), 0, st>>>(items, work, b); break;
         default: return hipErrorInvalidValue;
         }
         return hipGetLastError();

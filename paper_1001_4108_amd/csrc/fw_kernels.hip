@@ -54,6 +54,13 @@
 namespace fw {
 namespace {
 
+// 64-wide launches of at most this many tiles take two halves of k per tile
+// (512 threads): up to about two such workgroups per CU a launch lasts as
+// long as one of them (n=512 144 us against 178, n=1500, 529 bulk tiles, 608
+// against 650), beyond that the joining of the halves costs more than it
+// saves (n=2000, 961 tiles, 961 us against 857).
+constexpr int64_t kTile64SplitMax = 576;
+
 // A gated launch (gate != NULL) does nothing unless *gate != 0: the 64-bit
 // predecessor sweep queued behind a keyed one runs only when the keyed one
 // gave up.  The gate is uniform, so the whole workgroup leaves at once.
@@ -72,13 +79,14 @@ __device__ __forceinline__ bool given_up(const int32_t *flag) {
 }
 
 // Phase 1: closure of the diagonal tile (b, b) -- one workgroup.
-template <typename T, int S, int TM, bool PRED, class A>
-__global__ void __launch_bounds__((S / TM) * (S / TM))
+template <typename T, int S, bool PRED, class A>
+__global__ void __launch_bounds__((closure_threads<T, S, PRED, A, true>()))
 diag_kernel(T *__restrict__ d, int32_t *__restrict__ P, int n, int64_t ld, int64_t ldp,
             int b, int32_t *flag, const int32_t *gate) {
-    __shared__ __align__(16) char smem[closure_smem_bytes<T, S, PRED>()];
+    __shared__ __align__(16) char smem[closure_smem_bytes<T, S, PRED, true>()];
     if (gated_off(gate) || given_up<A>(flag)) return;
-    closure_tile_any<T, S, TM, PRED, A>(d, P, n, ld, ldp, b * S, smem, flag);
+    closure_tile_any<T, S, closure_tm<T, S, PRED, A, true>(), PRED, A,
+                     closure_tn<T, S, PRED, A, true>(), true>(d, P, n, ld, ldp, b * S, smem, flag);
 }
 
 // Phases 2 and 3: one tile per workgroup.
@@ -93,11 +101,6 @@ constexpr bool keyed_tile() {
     return PRED && std::is_same<T, int32_t>::value && std::is_same<A, Ar<int32_t>>::value &&
            FW_PRED_KEYS;
 }
-template <typename T, int S, int BK, bool PRED, class A>
-constexpr int tile_smem_bytes() {
-    return keyed_tile<T, S, BK, PRED, A>() ? product_key_smem_bytes<S, BK>()
-                                           : product_smem_bytes<T, S, BK, PRED>();
-}
 
 // Forms whose geometry is the closure's (4 x 4 cells per thread: tile 64 over
 // 256 threads, the 128-wide predecessor form over 1024) can also close the
@@ -109,11 +112,19 @@ constexpr bool tile_can_close() {
     return TM == 4 && TN == 4 && (S == 64 || (PRED && S == 128));
 }
 
+template <typename T, int S, int BK, int TM, int TN, bool PRED, class A>
+constexpr int tile_smem_bytes() {
+    const int product = keyed_tile<T, S, BK, PRED, A>() ? product_key_smem_bytes<S, BK>()
+                                                        : product_smem_bytes<T, S, BK, PRED>();
+    const int closure = tile_can_close<S, TM, TN, PRED>() ? closure_smem_bytes<T, S, PRED>() : 0;
+    return product > closure ? product : closure;
+}
+
 template <typename T, int S, int BK, int TM, int TN, bool VEC, bool PRED, class A>
 __global__ void __launch_bounds__((S / TM) * (S / TN))
 tile_kernel(T *__restrict__ d, int32_t *__restrict__ P, int n, int64_t ld, int64_t ldp, int b,
             int nb, int mode, int close_next, int32_t *flag, const int32_t *gate) {
-    __shared__ __align__(16) char smem[tile_smem_bytes<T, S, BK, PRED, A>()];
+    __shared__ __align__(16) char smem[tile_smem_bytes<T, S, BK, TM, TN, PRED, A>()];
     if (gated_off(gate) || given_up<A>(flag)) return;
     int idx = blockIdx.x, bi, bj;
     bool close = false;
@@ -135,8 +146,6 @@ tile_kernel(T *__restrict__ d, int32_t *__restrict__ P, int n, int64_t ld, int64
     else
         product_tile<T, S, BK, TM, TN, VEC, PRED, A>(d, P, n, ld, ldp, bi, bj, b, smem, flag);
     if constexpr (tile_can_close<S, TM, TN, PRED>()) {
-        static_assert(tile_smem_bytes<T, S, BK, PRED, A>() >= closure_smem_bytes<T, S, PRED>(),
-                      "the closure runs in the product's LDS");
         if (close) {
             __syncthreads();  // the tile's stores before its reloads
             closure_tile_any<T, S, TM, PRED, A>(d, P, n, ld, ldp, (b + 1) * S, smem, flag);
@@ -144,6 +153,67 @@ tile_kernel(T *__restrict__ d, int32_t *__restrict__ P, int n, int64_t ld, int64
     }
 }
 
+
+// Phases 2 and 3 at tile 64 without predecessors (product_tile_whole); mode
+// and CLOSE as tile_kernel's mode and close_next.
+// The closing form has the threads of the latency closure (closure_tm):
+// 512, and the wave that closes ahead.
+template <typename T, class A>
+constexpr int tile64_threads(int halves, bool close) {
+    const int closure = closure_threads<T, 64, false, A, true>();
+    return halves == 2 && close && closure > 512 ? closure : halves * 256;
+}
+template <typename T, int HALVES, bool CLOSE, bool VEC, class A>
+__global__ void __launch_bounds__((tile64_threads<T, A>(HALVES, CLOSE)))
+__attribute__((amdgpu_waves_per_eu(HALVES == 2 ? 3 : 1, 5)))
+tile64_kernel(T *__restrict__ d, int n, int64_t ld, int b, int nb, int mode, int32_t *flag,
+              const int32_t *gate) {
+    constexpr int S = 64;
+    static_assert(product_whole_smem_bytes<T>() >= closure_smem_bytes<T, S, false, true>(),
+                  "the closure runs in the product's LDS");
+    __shared__ __align__(16) char smem[product_whole_smem_bytes<T>()];
+    if (gated_off(gate) || given_up<A>(flag)) return;
+    int idx = blockIdx.x, bi, bj;
+    const int dix = b * (nb - 1) + b;  // tile (b+1, b+1), moved to blockIdx 0
+    if (CLOSE) idx = idx == 0 ? dix : idx == dix ? 0 : idx;
+    if (mode == 0)
+        panel_coords(idx, b, nb - 1, bi, bj);
+    else
+        bulk_coords(idx, b, nb - 1, bi, bj);
+    product_tile_whole<T, HALVES, VEC, A>(d, n, ld, bi, bj, b, smem, flag);
+    if constexpr (CLOSE) {
+        if (idx != dix) return;
+        constexpr bool kAhead = HALVES == 2 && closure_in_blocks<T, S, false, A>();
+        constexpr int TM = closure_tm<T, S, false, A, kAhead>();
+        constexpr int TN = closure_tn<T, S, false, A, kAhead>();
+        __syncthreads();  // the tile's stores before its reloads
+        if (kAhead || threadIdx.x < 256)
+            closure_tile_any<T, S, TM, false, A, TN, kAhead>(d, nullptr, n, ld, 0, (b + 1) * S,
+                                                             smem, flag);
+    }
+}
+
+template <typename T, int HALVES, class A>
+hipError_t tile64_launch(T *d, int n, int64_t ld, bool vec, int b, int nb, int mode, bool close,
+                         unsigned grid, hipStream_t st, int32_t *flag, const int32_t *gate) {
+    const int nt = tile64_threads<T, A>(HALVES, close);
+    if (close) {
+        if (vec)
+            tile64_kernel<T, HALVES, true, true, A><<<grid, nt, 0, st>>>(d, n, ld, b, nb, mode,
+                                                                        flag, gate);
+        else
+            tile64_kernel<T, HALVES, true, false, A><<<grid, nt, 0, st>>>(d, n, ld, b, nb, mode,
+                                                                         flag, gate);
+    } else {
+        if (vec)
+            tile64_kernel<T, HALVES, false, true, A><<<grid, nt, 0, st>>>(d, n, ld, b, nb, mode,
+                                                                         flag, gate);
+        else
+            tile64_kernel<T, HALVES, false, false, A><<<grid, nt, 0, st>>>(d, n, ld, b, nb, mode,
+                                                                          flag, gate);
+    }
+    return hipGetLastError();
+}
 
 // Phase 3 for 128-wide tiles without predecessors and with 16-byte aligned
 // rows: the bulk tiles among the first nf full blocks (blockIdx.x enumerates
@@ -541,13 +611,13 @@ hipError_t diag_t(int tile, T *d, int32_t *p, int n, int64_t ld, int64_t ldp, in
                   hipStream_t st, int32_t *flag, const int32_t *gate) {
     switch (tile) {
     case 128:
-        diag_kernel<T, 128, 4, PRED, A><<<1, 1024, 0, st>>>(d, p, n, ld, ldp, b, flag, gate);
+        diag_kernel<T, 128, PRED, A><<<1, closure_threads<T, 128, PRED, A, true>(), 0, st>>>(d, p, n, ld, ldp, b, flag, gate);
         break;
     case 64:
-        diag_kernel<T, 64, 4, PRED, A><<<1, 256, 0, st>>>(d, p, n, ld, ldp, b, flag, gate);
+        diag_kernel<T, 64, PRED, A><<<1, closure_threads<T, 64, PRED, A, true>(), 0, st>>>(d, p, n, ld, ldp, b, flag, gate);
         break;
     case 32:
-        diag_kernel<T, 32, 2, PRED, A><<<1, 256, 0, st>>>(d, p, n, ld, ldp, b, flag, gate);
+        diag_kernel<T, 32, PRED, A><<<1, closure_threads<T, 32, PRED, A, true>(), 0, st>>>(d, p, n, ld, ldp, b, flag, gate);
         break;
     default: return hipErrorInvalidValue;
     }
@@ -580,8 +650,11 @@ hipError_t tile_t(int tile, T *d, int32_t *p, int n, int64_t ld, int64_t ldp, in
         }
         break;
     case 64:
-        tile_kernel<T, 64, 16, 4, 4, VEC, PRED, A><<<grid, 256, 0, st>>>(
-            d, p, n, ld, ldp, b, nb, mode, close_next, flag, gate);
+        if constexpr (PRED)
+            tile_kernel<T, 64, 16, 4, 4, VEC, PRED, A><<<grid, 256, 0, st>>>(
+                d, p, n, ld, ldp, b, nb, mode, close_next, flag, gate);
+        else
+            return hipErrorInvalidValue;  // tile64_launch's
         break;
     case 32:
         tile_kernel<T, 32, 16, 4, 4, VEC, PRED, A><<<grid, 64, 0, st>>>(
@@ -639,10 +712,11 @@ hipError_t tile_dispatch(int tile, T *d, int32_t *p, int n, int64_t ld, int64_t 
         if (p) return hipErrorInvalidValue;
     }
     if (tile == 64)
-        return vec ? tile_t<T, true, false, A>(tile, d, p, n, ld, ldp, b, nb, mode,
-                                               (unsigned)grid, st, c, flag, gate)
-                   : tile_t<T, false, false, A>(tile, d, p, n, ld, ldp, b, nb, mode,
-                                                (unsigned)grid, st, c, flag, gate);
+        return grid <= kTile64SplitMax
+                   ? tile64_launch<T, 2, A>(d, n, ld, vec, b, nb, mode, close_next,
+                                            (unsigned)grid, st, flag, gate)
+                   : tile64_launch<T, 1, A>(d, n, ld, vec, b, nb, mode, close_next,
+                                            (unsigned)grid, st, flag, gate);
 #if FW_PANEL_STRIPS
     if (mode == 0 && tile == 128) {
         if (4 * grid > 0x7fffffffLL) return hipErrorInvalidValue;

@@ -17,6 +17,9 @@
 // written, i.e. the padded vertices are isolated and change no distance.
 #pragma once
 
+#include <type_traits>
+#include <utility>
+
 #include "fw_internal.h"
 
 namespace fw {
@@ -49,10 +52,12 @@ __device__ __forceinline__ float fmax32(float a, float b) {
 }
 
 // Every policy says whether its values need settle() before they are stored
-// or handed to other cells as operands (only the keyed policy does).
+// or handed to other cells as operands (only the keyed policy does).  top()
+// is the value that min2 and min3 leave out against any other.
 template <> struct Ar<float> {
     static constexpr bool kChecked = false;
     __device__ __forceinline__ static float inf() { return __builtin_inff(); }
+    __device__ __forceinline__ static float top() { return __builtin_inff(); }
     __device__ __forceinline__ static float add(float a, float b) { return a + b; }
     __device__ __forceinline__ static float min2(float a, float b) { return fmin32(a, b); }
     __device__ __forceinline__ static float min3(float a, float b, float c) {
@@ -65,6 +70,7 @@ template <> struct Ar<float> {
 template <> struct Ar<int32_t> {
     static constexpr bool kChecked = false;
     __device__ __forceinline__ static int32_t inf() { return kI32Inf; }
+    __device__ __forceinline__ static int32_t top() { return 0x7fffffff; }
     __device__ __forceinline__ static int32_t add(int32_t a, int32_t b) {
         return (int32_t)((uint32_t)a + (uint32_t)b);
     }
@@ -86,6 +92,7 @@ template <typename T> struct ArMaxMin;
 template <> struct ArMaxMin<float> {
     static constexpr bool kChecked = false;
     __device__ __forceinline__ static float inf() { return -__builtin_inff(); }
+    __device__ __forceinline__ static float top() { return -__builtin_inff(); }
     __device__ __forceinline__ static float add(float a, float b) { return fmin32(a, b); }
     __device__ __forceinline__ static float min2(float a, float b) { return fmax32(a, b); }
     __device__ __forceinline__ static float min3(float a, float b, float c) {
@@ -96,6 +103,7 @@ template <> struct ArMaxMin<float> {
 template <> struct ArMaxMin<int32_t> {
     static constexpr bool kChecked = false;
     __device__ __forceinline__ static int32_t inf() { return (int32_t)0x80000000; }
+    __device__ __forceinline__ static int32_t top() { return (int32_t)0x80000000; }
     __device__ __forceinline__ static int32_t add(int32_t a, int32_t b) { return a < b ? a : b; }
     __device__ __forceinline__ static int32_t min2(int32_t a, int32_t b) { return a > b ? a : b; }
     __device__ __forceinline__ static int32_t min3(int32_t a, int32_t b, int32_t c) {
@@ -130,6 +138,7 @@ struct KeyCheck {
 struct ArKey {
     static constexpr bool kChecked = true;
     __device__ __forceinline__ static int32_t inf() { return kKeyInf; }
+    __device__ __forceinline__ static int32_t top() { return 0x7fffffff; }
     __device__ __forceinline__ static int32_t add(int32_t a, int32_t b) {
         return (int32_t)(((uint32_t)a & ~(uint32_t)kKeyHop) + (uint32_t)b);
     }
@@ -257,11 +266,13 @@ __device__ __forceinline__ void row_store(const T (&v)[E], T *__restrict__ base,
 // suffices.  The TM steps of one register row are unrolled so the owner's
 // register index is a compile-time constant.
 // ---------------------------------------------------------------------------
-// (without predecessors: room for closure_tile_pairs' double-buffered rows
-// and columns k and k+1)
-template <typename T, int S, bool PRED>
+// (without predecessors: closure_blocks' two buffers of 8 rows and of 8
+// columns, its small ones, and ahead one more of 8 columns)
+constexpr int kCloseExtra = 2 * 8 * 12 + 2 * 8 * 8;
+template <typename T, int S, bool PRED, bool AHEAD = false>
 constexpr int closure_smem_bytes() {
-    return PRED ? 4 * S * (int)sizeof(T) + 2 * S * 4 : 8 * S * (int)sizeof(T);
+    return PRED ? 4 * S * (int)sizeof(T) + 2 * S * 4
+                : ((AHEAD ? 40 : 32) * S + kCloseExtra) * (int)sizeof(T);
 }
 
 // FULL: the caller guarantees a tile inside the matrix with 16-byte aligned
@@ -390,101 +401,361 @@ __device__ __forceinline__ void closure_tile(T *__restrict__ d, int32_t *__restr
     __syncthreads();
 }
 
-// closure_tile two k-steps per barrier, with closure_tile's bits (no
-// predecessors, no range-checked keys; TM x TM cells per thread, TM even).
-// Before steps k and k+1 (k even) the owners publish rows k, k+1 and columns
-// k, k+1 as they stand.  Every thread then forms row k+1 and column k+1 as
-// step k leaves them -- c[k+1][j] <- c[k+1][j] + (c[k+1][k] x c[k][j]), and
-// c[i][k+1] <- c[i][k+1] + (c[i][k] x c[k][k+1]) in the semiring's (+, x) --
-// and applies both steps at once with one 3-input reduction:
-// c[i][j] <- c[i][j] + c[i][k] x c[k][j] + c'[i][k+1] x c'[k+1][j].  These are
-// the same operations on the same values as the two steps in turn, so the
-// result is bit-identical for any weights.  Half the barriers of closure_tile
-// for the same VALU count.  Steps past the last vertex (the padded k that
-// rounds an odd count up) change no real cell: the padded rows and columns
-// are absent.
-template <typename T, int S, int TM, class A = Ar<T>>
-__device__ __forceinline__ void closure_tile_pairs(T *__restrict__ d, int n, int64_t ld, int base,
-                                                   char *smem) {
-    static_assert(TM % 2 == 0, "a thread owns both rows (columns) of a step pair");
-    static_assert(!A::kChecked, "range-checked keys take closure_tile");
-    constexpr int G = S / TM;
-    T(*rowb)[2][S] = reinterpret_cast<T(*)[2][S]>(smem);  // [parity][k, k+1][S]
-    T(*colb)[2][S] = reinterpret_cast<T(*)[2][S]>(smem + 4 * S * sizeof(T));
-    const int tx = threadIdx.x % G, ty = threadIdx.x / G;
-    T c[TM][TM];
-#pragma unroll
-    for (int r = 0; r < TM; ++r) {
-        const int gi = base + ty * TM + r;
-#pragma unroll
-        for (int q = 0; q < TM; ++q) {
-            const int gj = base + tx * TM + q;
-            c[r][q] = (gi < n && gj < n) ? d[(int64_t)gi * ld + gj] : A::inf();
-        }
-    }
-    const int kreal = n - base < S ? n - base : S;
-    const int kb_end = (kreal + TM - 1) / TM;
-    for (int kb = 0; kb < kb_end; ++kb) {
-#pragma unroll
-        for (int rp = 0; rp < TM; rp += 2) {
-            const int buf = ((kb * TM + rp) >> 1) & 1;
-            if (ty == kb) {
-#pragma unroll
-                for (int q = 0; q < TM; ++q) {
-                    rowb[buf][0][tx * TM + q] = c[rp][q];
-                    rowb[buf][1][tx * TM + q] = c[rp + 1][q];
-                }
-            }
-            if (tx == kb) {
-#pragma unroll
-                for (int q = 0; q < TM; ++q) {
-                    colb[buf][0][ty * TM + q] = c[q][rp];
-                    colb[buf][1][ty * TM + q] = c[q][rp + 1];
-                }
-            }
-            __syncthreads();
-            const int k = kb * TM + rp;
-            const T a = colb[buf][0][k + 1];  // c[k+1][k]
-            const T e = rowb[buf][0][k + 1];  // c[k][k+1]
-            T r0[TM], r1[TM], c0[TM], c1[TM];
-#pragma unroll
-            for (int q = 0; q < TM; ++q) {
-                r0[q] = rowb[buf][0][tx * TM + q];
-                r1[q] = A::min2(rowb[buf][1][tx * TM + q], A::add(a, r0[q]));
-                c0[q] = colb[buf][0][ty * TM + q];
-                c1[q] = A::min2(colb[buf][1][ty * TM + q], A::add(c0[q], e));
-            }
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int j = 0; j < TM; ++j)
-                    c[i][j] = A::min3(c[i][j], A::add(c0[i], r0[j]), A::add(c1[i], r1[j]));
-        }
-    }
-#pragma unroll
-    for (int r = 0; r < TM; ++r) {
-        const int gi = base + ty * TM + r;
-#pragma unroll
-        for (int q = 0; q < TM; ++q) {
-            const int gj = base + tx * TM + q;
-            if (gi < n && gj < n) d[(int64_t)gi * ld + gj] = c[r][q];
-        }
-    }
+// Lane K (compile-time) of every 16-lane row, broadcast to that row.
+template <int K, typename T>
+__device__ __forceinline__ T row_lane(T v) {
+    const int x = __builtin_bit_cast(int, v);
+    return __builtin_bit_cast(T, __builtin_amdgcn_update_dpp(x, x, 0x150 + K, 0xf, 0xf, true));
 }
 
-// The diagonal closure in the form its arguments allow: two k-steps per
-// barrier without predecessors or range-checked keys, else closure_tile.
-#ifndef FW_CLOSURE_PAIRS
-#define FW_CLOSURE_PAIRS 1
+// The 16-lane row Q (compile-time) of the wave, copied to all four rows: the
+// halves exchanged, then the odd and even rows.
+template <int Q, typename T>
+__device__ __forceinline__ T wave_row(T v) {
+    const unsigned x = __builtin_bit_cast(unsigned, v);
+    const auto half = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+    const unsigned u = half[Q >> 1];
+    const auto row = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    return __builtin_bit_cast(T, (unsigned)row[Q & 1]);
+}
+
+// Calls f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>).
+template <class F, int... I>
+__device__ __forceinline__ void static_for_seq(F &&f, std::integer_sequence<int, I...>) {
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void static_for(F &&f) {
+    static_for_seq(f, std::make_integer_sequence<int, N>{});
+}
+
+// close8: the closure of an 8 x 8 block by one wave.  Lane 16 g + q holds D[r] =
+// the block's entry (2 g + r, q % 8).  Rows are taken in pairs: rows 2 g and
+// 2 g + 1 are spread to the whole wave by lane swaps (the two independent, so
+// their latencies overlap), the second brought forward by the first, and then
+// applied; column k is a row broadcast folded into the add.  The same sums as
+// eight plain steps.
+constexpr int kClosureK = 8;
+template <class A, typename T>
+__device__ __forceinline__ void close8(T (&D)[2]) {
+    static_for<kClosureK / 2>([&](auto gc) {
+        constexpr int g = decltype(gc)::value;
+        const T r0 = wave_row<g>(D[0]);
+        T r1 = wave_row<g>(D[1]);
+        r1 = A::min2(r1, A::add(row_lane<2 * g>(r1), r0));
+#pragma unroll
+        for (int r = 0; r < 2; ++r) D[r] = A::min2(D[r], A::add(row_lane<2 * g>(D[r]), r0));
+#pragma unroll
+        for (int r = 0; r < 2; ++r) D[r] = A::min2(D[r], A::add(row_lane<2 * g + 1>(D[r]), r1));
+    });
+}
+
+// x + sum over p < 8 of a_p x b_p in the semiring's (+, x), each of a and b
+// given as two pieces of four.
+template <class A, typename T, typename V4>
+__device__ __forceinline__ T sum8(T x, V4 a0, V4 a1, V4 b0, V4 b1) {
+    x = A::min3(x, A::add((T)a0[0], (T)b0[0]), A::add((T)a0[1], (T)b0[1]));
+    x = A::min3(x, A::add((T)a0[2], (T)b0[2]), A::add((T)a0[3], (T)b0[3]));
+    x = A::min3(x, A::add((T)a1[0], (T)b1[0]), A::add((T)a1[1], (T)b1[1]));
+    return A::min3(x, A::add((T)a1[2], (T)b1[2]), A::add((T)a1[3], (T)b1[3]));
+}
+
+// closure_blocks: closure_tile in 8-vertex sub-blocks K instead of single
+// steps (no predecessors, no range-checked keys).  For each K in turn, with
+// D the closure of (K, K) and R the rows of K as they stand before it:
+//   E_iq <- c_iq + sum over p in K of c_ip x D_pq  (the columns K of row i),
+//   c_ij <- c_ij + sum over q in K of E_iq x R_qj  in the semiring's (+, x):
+// a path through K enters it by one old entry, goes on inside K, and leaves
+// it by one old entry (for i in K itself E is D).
+// What bounds a closure is its serial chain, so the 8 steps of (K, K) run in
+// one wave's registers, without LDS or barriers.
+//   AHEAD false: the first wave closes (K, K) between two barriers.
+//   AHEAD true: one more wave than the cells need does nothing else: while the
+//     others update the cells by K, it forms the next sub-block's (K', K')
+//     from E and R, the same sums as the owners of those cells, and closes
+//     it.  One barrier per sub-block.
+// Threads: (S / TM) x (S / TN) (+ 64), S / TN a multiple of 16.  A thread owns
+// rows ty * TM .., and of every 4 (S / TN) columns the four at 4 tx (of all S
+// the two at 2 tx where TN = 2).  A wave forms the E of its own rows, so no
+// barrier lies between that and their use.  LDS, all but e in pairs used in
+// turn (a buffer is written again only after a barrier that follows its last
+// read): r, the rows of K (8 x S); c, the columns (S x 8); e, E (S x 8; over c
+// where no wave reads ahead of its owner); dt, D by columns; t, the next
+// (K', K') as its owners hold it.
+// Every geometry and both forms take the same sums, so a tile's bits do not
+// depend on them.
+// Measured (one 64-wide tile, launches back to back): 9.4 us ahead (512 + 64
+// threads), 13.2 us in 256 threads, against 12 us and, in a 256-thread bulk
+// workgroup, 13 us for two plain steps per barrier; 16-vertex sub-blocks
+// took 9.8 us (the closing wave's share grows with the square of their width).
+// 128-wide: 31 us ahead against 37 us.
+constexpr int kCloseLd = kClosureK + 4;  // 16-byte pieces of D's columns in different banks
+static_assert(kCloseExtra == 2 * kClosureK * kCloseLd + 2 * kClosureK * kClosureK, "dt, t");
+template <typename T>
+struct ClosureLds {
+    T *r0, *r1, *c0, *c1;
+    T *extra;  // kCloseExtra values: dt[2], t[2]
+    T *e;      // 8 x S, AHEAD only
+};
+
+template <typename T, int S, int TM, int TN, class A, bool FULL, bool AHEAD = false>
+__device__ __forceinline__ void closure_blocks(T *__restrict__ d, int n, int64_t ld, int base,
+                                               const ClosureLds<T> &lds) {
+    static_assert(!A::kChecked, "range-checked keys take closure_tile");
+    constexpr int K = kClosureK, G = S / TN, NW = (S / TM) * (S / TN);
+    constexpr int CW = TN < 4 ? TN : 4;           // piece of a row
+    constexpr int WR = 64 / G * TM, M = WR / 8;   // rows of a wave; its E per lane
+    constexpr int QS = AHEAD ? 4 : 2;             // of K per step of the update
+    static_assert(G % 16 == 0 && TN % CW == 0 && K % TM == 0 && WR % 8 == 0, "geometry");
+    typedef typename Vec4<T>::type V4;
+    typedef T VW __attribute__((ext_vector_type(CW)));
+    typedef T VQ __attribute__((ext_vector_type(QS)));
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const bool ahead = AHEAD && wave == NW / 64;  // the wave that closes ahead
+    const bool closer = AHEAD ? ahead : wave == 0;
+    // its chain is the closure's: ahead of the waves it shares a SIMD with
+    if (ahead) __builtin_amdgcn_s_setprio(3);
+    int tx = threadIdx.x % G, ty = threadIdx.x / G;
+    const int lane = threadIdx.x & 63, g = lane >> 4, cq = lane & 7;
+    // a tile inside the matrix with 16-byte aligned rows (FULL: the caller
+    // guarantees it) moves in 16-byte pieces
+    const bool full = FULL || (base + S <= n && (uintptr_t)d % 16 == 0 && ld % 4 == 0);
+    T c[TM][TN], D[2];
+    if (!ahead) {
+#pragma unroll
+        for (int r = 0; r < TM; ++r)
+#pragma unroll
+            for (int h = 0; h < TN / CW; ++h) {
+                T v[CW];
+                row_load<T, CW, CW == 4>(v, d, base + ty * TM + r, base + h * CW * G + tx * CW, n,
+                                         ld, full, A::inf());
+#pragma unroll
+                for (int e = 0; e < CW; ++e) c[r][CW * h + e] = v[e];
+            }
+    } else {
+        // the first (K, K), straight from the matrix
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            T v[1];
+            row_load<T, 1, false>(v, d, base + 2 * g + r, base + cq, n, ld, full, A::inf());
+            D[r] = v[0];
+        }
+    }
+    auto put_closed = [&](T *dt) {
+        close8<A>(D);
+        dt[cq * kCloseLd + 2 * g] = D[0];
+        dt[cq * kCloseLd + 2 * g + 1] = D[1];
+    };
+    if (ahead) put_closed(lds.extra);
+    // sub-blocks past the last vertex hold padded (isolated) vertices only
+    const int kreal = n - base < S ? n - base : S;
+    const int blocks = (kreal + K - 1) / K;
+#pragma unroll 1
+    for (int s = 0; s < blocks; ++s) {
+        T *R = s & 1 ? lds.r1 : lds.r0, *C = s & 1 ? lds.c1 : lds.c0;
+        T *dt = lds.extra + (s & 1) * K * kCloseLd;
+        T *next = lds.extra + 2 * K * kCloseLd + (s & 1) * K * K;
+        if (!ahead) {
+            // opaque (no instruction is emitted): LDS addresses are formed
+            // anew in each sub-block instead of kept in registers
+            asm volatile("" : "+v"(tx), "+v"(ty));
+            const int rb = ty / (K / TM), row = (ty % (K / TM)) * TM;  // row block, row in it
+            if (rb == s) {
+#pragma unroll
+                for (int r = 0; r < TM; ++r)
+#pragma unroll
+                    for (int h = 0; h < TN / CW; ++h) {
+                        VW x;
+#pragma unroll
+                        for (int e = 0; e < CW; ++e) x[e] = c[r][CW * h + e];
+                        *reinterpret_cast<VW *>(R + (row + r) * S + h * CW * G + tx * CW) = x;
+                    }
+            }
+#pragma unroll
+            for (int h = 0; h < TN / CW; ++h) {
+                const int cb = h * (CW * G / K) + tx / (K / CW);  // column block
+                const int col = CW * (tx % (K / CW));
+                if (cb == s || (AHEAD && cb == s + 1 && rb == s + 1)) {
+                    T *dst = cb == s ? C + ty * TM * K + col : next + row * K + col;
+#pragma unroll
+                    for (int r = 0; r < TM; ++r) {
+                        VW x;
+#pragma unroll
+                        for (int e = 0; e < CW; ++e) x[e] = c[r][CW * h + e];
+                        *reinterpret_cast<VW *>(dst + r * K) = x;
+                    }
+                }
+            }
+        }
+        __syncthreads();
+        if constexpr (!AHEAD) {
+            if (closer) {
+                D[0] = R[2 * g * S + s * K + cq];
+                D[1] = R[(2 * g + 1) * S + s * K + cq];
+                put_closed(dt);
+            }
+            __syncthreads();
+        }
+        if (ahead) {
+            if (s + 1 < blocks) {
+                const T *old = C + ((s + 1) * K + 2 * g) * K;  // rows 2 g, 2 g + 1 of K'
+                const V4 d0 = *reinterpret_cast<const V4 *>(dt + cq * kCloseLd);
+                const V4 d1 = *reinterpret_cast<const V4 *>(dt + cq * kCloseLd + 4);
+                T E[2], b[K];
+#pragma unroll
+                for (int p = 0; p < K; ++p) b[p] = R[p * S + (s + 1) * K + cq];
+#pragma unroll
+                for (int r = 0; r < 2; ++r) {
+                    const V4 a0 = *reinterpret_cast<const V4 *>(old + r * K);
+                    const V4 a1 = *reinterpret_cast<const V4 *>(old + r * K + 4);
+                    E[r] = sum8<A, T>(old[r * K + cq], a0, a1, d0, d1);
+                    D[r] = next[(2 * g + r) * K + cq];
+                }
+                static_for<K / 2>([&](auto pc) {
+                    constexpr int p = 2 * decltype(pc)::value;
+#pragma unroll
+                    for (int r = 0; r < 2; ++r)
+                        D[r] = A::min3(D[r], A::add(row_lane<p>(E[r]), b[p]),
+                                       A::add(row_lane<p + 1>(E[r]), b[p + 1]));
+                });
+                put_closed(lds.extra + ((s + 1) & 1) * K * kCloseLd);
+            }
+        } else {
+            // E of the wave's rows, a lane per column and eight rows at a time
+            T *W = AHEAD ? lds.e : C;
+            {
+                const int row = wave * WR + (lane >> 3);
+                const V4 d0 = *reinterpret_cast<const V4 *>(dt + cq * kCloseLd);
+                const V4 d1 = *reinterpret_cast<const V4 *>(dt + cq * kCloseLd + 4);
+                T E[M];
+#pragma unroll
+                for (int m = 0; m < M; ++m) {
+                    const T *old = C + (row + 8 * m) * K;
+                    const V4 a0 = *reinterpret_cast<const V4 *>(old);
+                    const V4 a1 = *reinterpret_cast<const V4 *>(old + 4);
+                    E[m] = sum8<A, T>(old[cq], a0, a1, d0, d1);
+                }
+#pragma unroll
+                for (int m = 0; m < M; ++m) W[(row + 8 * m) * K + cq] = E[m];
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            // QS of K a step; with AHEAD the next step's operands are read
+            // before these are used (the scheduling barriers keep them there)
+            T ea[2][QS][TM], rr[2][QS][TN];
+            auto read = [&](int k, T(&x)[QS][TM], T(&y)[QS][TN]) {
+#pragma unroll
+                for (int r = 0; r < TM; ++r) {
+                    const VQ v = *reinterpret_cast<const VQ *>(W + (ty * TM + r) * K + k);
+#pragma unroll
+                    for (int f = 0; f < QS; ++f) x[f][r] = v[f];
+                }
+#pragma unroll
+                for (int f = 0; f < QS; ++f)
+#pragma unroll
+                    for (int h = 0; h < TN / CW; ++h) {
+                        const VW v =
+                            *reinterpret_cast<const VW *>(R + (k + f) * S + h * CW * G + tx * CW);
+#pragma unroll
+                        for (int e = 0; e < CW; ++e) y[f][CW * h + e] = v[e];
+                    }
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            auto apply = [&](T(&x)[QS][TM], T(&y)[QS][TN]) {
+#pragma unroll
+                for (int f = 0; f < QS; f += 2)
+#pragma unroll
+                    for (int r = 0; r < TM; ++r)
+#pragma unroll
+                        for (int j = 0; j < TN; ++j)
+                            c[r][j] = A::min3(c[r][j], A::add(x[f][r], y[f][j]),
+                                              A::add(x[f + 1][r], y[f + 1][j]));
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            if constexpr (AHEAD) {
+                static_assert(K == 2 * QS, "two steps");
+                read(0, ea[0], rr[0]);
+                read(QS, ea[1], rr[1]);
+                apply(ea[0], rr[0]);
+                apply(ea[1], rr[1]);
+            } else {
+#pragma unroll 1
+                for (int k = 0; k < K; k += QS) {
+                    read(k, ea[0], rr[0]);
+                    apply(ea[0], rr[0]);
+                }
+            }
+        }
+    }
+    // store addresses from opaque copies, not kept live through the steps
+    int sty = ty, stx = tx;
+    asm volatile("" : "+v"(sty), "+v"(stx));
+    if (!ahead) {
+#pragma unroll
+        for (int r = 0; r < TM; ++r)
+#pragma unroll
+            for (int h = 0; h < TN / CW; ++h) {
+                T v[CW];
+#pragma unroll
+                for (int e = 0; e < CW; ++e) v[e] = c[r][CW * h + e];
+                row_store<T, CW, CW == 4>(v, d, base + sty * TM + r, base + h * CW * G + stx * CW,
+                                          n, ld, full);
+            }
+    }
+    if (ahead) __builtin_amdgcn_s_setprio(0);
+    // the LDS buffers may be reused by the caller right away
+    __syncthreads();
+}
+
+// The diagonal closure in the form its arguments allow: in sub-blocks without
+// predecessors or range-checked keys, else closure_tile.
+template <typename T, int S, bool PRED, class A = Ar<T>>
+constexpr bool closure_in_blocks() {
+    return !PRED && !A::kChecked;
+}
+// Cells per thread (rows, columns) and threads of a diagonal launch's closure.
+// AHEAD (one tile, latency): 512 threads and the wave that closes ahead, so
+// that updating the cells takes no longer than its chain.  Many tiles
+// (throughput): 256 threads.
+#ifndef FW_CLOSURE64_TM
+#define FW_CLOSURE64_TM 2
+#define FW_CLOSURE64_TN 4
 #endif
-template <typename T, int S, int TM, bool PRED, class A = Ar<T>>
+#ifndef FW_CLOSURE128_TM
+#define FW_CLOSURE128_TM 4
+#define FW_CLOSURE128_TN 8
+#endif
+template <typename T, int S, bool PRED, class A, bool AHEAD>
+constexpr int closure_tm() {
+    if (S == 32) return 2;
+    if (!closure_in_blocks<T, S, PRED, A>()) return 4;
+    return S == 64 ? (AHEAD ? FW_CLOSURE64_TM : 4) : (AHEAD ? FW_CLOSURE128_TM : 8);
+}
+template <typename T, int S, bool PRED, class A, bool AHEAD>
+constexpr int closure_tn() {
+    if (S == 32) return 2;
+    if (!closure_in_blocks<T, S, PRED, A>()) return 4;
+    return S == 64 ? (AHEAD ? FW_CLOSURE64_TN : 4) : (AHEAD ? FW_CLOSURE128_TN : 8);
+}
+template <typename T, int S, bool PRED, class A, bool AHEAD>
+constexpr int closure_threads() {
+    return (S / closure_tm<T, S, PRED, A, AHEAD>()) * (S / closure_tn<T, S, PRED, A, AHEAD>()) +
+           (AHEAD && closure_in_blocks<T, S, PRED, A>() ? 64 : 0);
+}
+template <typename T, int S, int TM, bool PRED, class A = Ar<T>, int TN = TM, bool AHEAD = false>
 __device__ __forceinline__ void closure_tile_any(T *__restrict__ d, int32_t *__restrict__ P, int n,
                                                  int64_t ld, int64_t ldp, int base, char *smem,
                                                  int32_t *flag = nullptr) {
-    if constexpr (FW_CLOSURE_PAIRS && !PRED && !A::kChecked && TM % 2 == 0)
-        closure_tile_pairs<T, S, TM, A>(d, n, ld, base, smem);
-    else
+    if constexpr (closure_in_blocks<T, S, PRED, A>()) {
+        T *b = reinterpret_cast<T *>(smem);
+        constexpr int W = kClosureK * S;
+        const ClosureLds<T> lds = {b, b + W, b + 2 * W, b + 3 * W, b + 4 * W, b + 4 * W + kCloseExtra};
+        closure_blocks<T, S, TM, TN, A, false, AHEAD>(d, n, ld, base, lds);
+    } else {
+        static_assert(TM == TN, "closure_tile has square sub-tiles");
         closure_tile<T, S, TM, PRED, A>(d, P, n, ld, ldp, base, smem, flag);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -634,6 +905,161 @@ __device__ __forceinline__ void product_tile(T *__restrict__ d, int32_t *__restr
 }
 
 // ---------------------------------------------------------------------------
+// product_tile_whole: the 64 x 64 tile update of product_tile (no
+// predecessors), bound by latency: the whole 64-deep k-block is staged at
+// once, so one memory latency and one barrier replace four of each, and the k
+// loop runs through with the next LDS reads in flight (88 registers, five
+// waves per SIMD; product_tile's loop, made for six, waits on each).
+// HALVES * 256 threads (any further ones only keep the barriers), 4 x 4 cells
+// each; with two halves each takes 32 of the k, the second from top() on, and
+// the first joins the two and stores.  LDS: A row-major, the 16-byte piece p
+// of row r at p ^ (r / 4) (the 4 rows a wave reads at once fall in different
+// banks), B as in memory.  Same candidates as product_tile, hence the same
+// bits.  Measured (with the closure above): n=512 fp32 252 -> 144 us, n=1500
+// 804 -> 608 us, and, at one half per tile and five workgroups per CU, n=4096
+// 3.26 -> 2.65 ms: the read-ahead loop also beats product_tile's where the
+// launch fills the GPU.
+// ---------------------------------------------------------------------------
+template <typename T>
+constexpr int product_whole_smem_bytes() {
+    return 2 * 64 * 64 * (int)sizeof(T);
+}
+
+template <typename T, int HALVES, bool VEC, class A = Ar<T>>
+__device__ __forceinline__ void product_tile_whole(T *__restrict__ d, int n, int64_t ld, int bi,
+                                                   int bj, int b, char *smem,
+                                                   int32_t *flag = nullptr) {
+    constexpr int S = 64, TM = 4, P = 4 / HALVES;  // P: 16-row groups a thread stages
+    typedef typename Vec4<T>::type V4;
+    T *As = reinterpret_cast<T *>(smem), *Bs = As + S * S;
+    const int half = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8);
+    const int tid = threadIdx.x & 255, tx = tid & 15, ty = tid >> 4;
+    const int64_t row0 = (int64_t)bi * S, col0 = (int64_t)bj * S, k0 = (int64_t)b * S;
+    const bool full = (row0 + S <= n) && (col0 + S <= n) && (k0 + S <= n);
+    V4 acc[TM];
+    if (half < HALVES) {
+        V4 ra[P], rb[P];
+        const int sr = half * P * 16 + ty;  // first row staged
+        if (VEC && full) {
+#pragma unroll
+            for (int i = 0; i < P; ++i) {
+                ra[i] = *reinterpret_cast<const V4 *>(d + (row0 + sr + i * 16) * ld + k0 + tx * 4);
+                rb[i] = *reinterpret_cast<const V4 *>(d + (k0 + sr + i * 16) * ld + col0 + tx * 4);
+            }
+            if (half == 0) {
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+                    acc[i] = *reinterpret_cast<const V4 *>(d + (row0 + ty * TM + i) * ld + col0 +
+                                                           tx * 4);
+            }
+        } else {
+            // addresses clamped into the matrix, so that every load is issued
+            // before the first is waited for; what lies outside reads as absent
+            auto at = [&](int64_t r, int64_t c) {
+                const T v = d[(r < n ? r : n - 1) * ld + (c < n ? c : n - 1)];
+                return r < n && c < n ? v : A::inf();
+            };
+#pragma unroll
+            for (int i = 0; i < P; ++i)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    ra[i][e] = at(row0 + sr + i * 16, k0 + tx * 4 + e);
+                    rb[i][e] = at(k0 + sr + i * 16, col0 + tx * 4 + e);
+                }
+            if (half == 0) {
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        acc[i][e] = at(row0 + ty * TM + i, col0 + tx * 4 + e);
+            }
+        }
+        if (half != 0) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[i][e] = A::top();
+        }
+#pragma unroll
+        for (int i = 0; i < P; ++i) {
+            const int r = sr + i * 16;
+            *reinterpret_cast<V4 *>(As + r * S + (tx ^ (r >> 2)) * 4) = ra[i];
+            *reinterpret_cast<V4 *>(Bs + r * S + tx * 4) = rb[i];
+        }
+    }
+    __syncthreads();
+    if (half < HALVES) {
+        // four k a step, the next step's operands read before this one's use
+        // (the scheduling barriers keep the reads there)
+        constexpr int STEPS = S / HALVES / 4;
+        const int s0 = half * STEPS;
+        V4 a[2][TM], bb[2][4];
+        auto read = [&](int s, V4(&x)[TM], V4(&y)[4]) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+                x[i] = *reinterpret_cast<const V4 *>(As + (ty * TM + i) * S + (s ^ ty) * 4);
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                y[e] = *reinterpret_cast<const V4 *>(Bs + (4 * s + e) * S + tx * 4);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        auto apply = [&](V4(&x)[TM], V4(&y)[4]) {
+#pragma unroll
+            for (int e = 0; e < 4; e += 2)
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int j = 0; j < TM; ++j)
+                        acc[i][j] = A::min3(acc[i][j], A::add(x[i][e], y[e][j]),
+                                            A::add(x[i][e + 1], y[e + 1][j]));
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        read(s0, a[0], bb[0]);
+#pragma unroll 1
+        for (int t = 0; t < STEPS; t += 2) {
+            read(s0 + t + 1, a[1], bb[1]);
+            apply(a[0], bb[0]);
+            // (the last step reads the block's first operands again)
+            read(t + 2 < STEPS ? s0 + t + 2 : s0, a[0], bb[0]);
+            apply(a[1], bb[1]);
+        }
+    }
+    if constexpr (HALVES == 2) {
+        __syncthreads();
+        V4 *part = reinterpret_cast<V4 *>(smem);
+        if (half == 1) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i) part[i * 256 + tid] = acc[i];
+        }
+        __syncthreads();
+        if (half == 0) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i) {
+                const V4 x = part[i * 256 + tid];
+#pragma unroll
+                for (int j = 0; j < TM; ++j) acc[i][j] = A::min2(acc[i][j], x[j]);
+            }
+        }
+    }
+    if (half != 0) return;
+    if constexpr (A::kChecked) {
+        KeyCheck bad;
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TM; ++j) acc[i][j] = settle<A>(acc[i][j], bad);
+        raise_flag<A>(flag, bad);
+    }
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+        T v[TM];
+#pragma unroll
+        for (int j = 0; j < TM; ++j) v[j] = acc[i][j];
+        row_store<T, TM, VEC>(v, d, (int)row0 + ty * TM + i, (int)col0 + tx * TM, n, ld, full);
+    }
+}
+
+// ---------------------------------------------------------------------------
 // bulk_tile_dma: the 128 x 128 tile update of product_tile (no predecessors)
 // for a tile that lies inside the matrix with a full k-block, the k-slices
 // moved from global memory straight into LDS by gfx950's global->LDS dwordx4
@@ -682,6 +1108,7 @@ __device__ __forceinline__ void bulk_tile_dma(T *__restrict__ d, int n, int64_t 
     __shared__ __align__(16) T A1[S * BK];
     __shared__ __align__(16) T B0[BK * S];
     __shared__ __align__(16) T B1[BK * S];
+    __shared__ __align__(16) T X[kCloseExtra];  // the closure's
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -809,8 +1236,12 @@ __device__ __forceinline__ void bulk_tile_dma(T *__restrict__ d, int n, int64_t 
         // barrier orders its stores before the loads) and closed in place;
         // the product's LDS buffers are free by now
         __syncthreads();
-        closure_tile<T, S, TM, false, A, true>(d, nullptr, n, ld, 0, (int)row0,
-                                               reinterpret_cast<char *>(A0), flag);
+        if constexpr (closure_in_blocks<T, S, false, A>())
+            closure_blocks<T, S, TM, TM, A, true>(d, n, ld, (int)row0,
+                                                  ClosureLds<T>{B0, B1, A0, A1, X, nullptr});
+        else
+            closure_tile<T, S, TM, false, A, true>(d, nullptr, n, ld, 0, (int)row0,
+                                                   reinterpret_cast<char *>(A0), flag);
     }
 }
 
