@@ -31,21 +31,10 @@
 
 #include "fw_tiles.h"
 
-// Build-time switches (variant builds override them with -D): the direct
-// global->LDS bulk kernel, keyed int32 predecessor tiles, the next diagonal
-// closed inside the bulk launch, strip-split panels, waves per SIMD of the
-// bulk kernel.
-#ifndef FW_BULK_DMA
-#define FW_BULK_DMA 1
-#endif
+// Build-time switches (variant builds override them with -D): keyed int32
+// predecessor tiles, waves per SIMD of the bulk kernel.
 #ifndef FW_PRED_KEYS
 #define FW_PRED_KEYS 1
-#endif
-#ifndef FW_FUSE_DIAG
-#define FW_FUSE_DIAG 1
-#endif
-#ifndef FW_PANEL_STRIPS
-#define FW_PANEL_STRIPS 1
 #endif
 #ifndef FW_BULK_DMA_WAVES
 #define FW_BULK_DMA_WAVES 4
@@ -91,10 +80,7 @@ diag_kernel(T *__restrict__ d, int32_t *__restrict__ P, int n, int64_t ld, int64
 
 // Phases 2 and 3: one tile per workgroup.
 //   mode 0: blockIdx.x enumerates the 2(nb-1) panel tiles of stage b;
-//   mode 1: blockIdx.x enumerates the (nb-1)^2 bulk tiles;
-//   mode 2: the 2(nb-1)-1 bulk tiles in the last block row or column (the
-//           part of the bulk that bulk_dma_kernel leaves when the last block
-//           is partial).
+//   mode 1: blockIdx.x enumerates the (nb-1)^2 bulk tiles.
 // int32 with predecessors takes the keyed form (product_tile_key).
 template <typename T, int S, int BK, bool PRED, class A>
 constexpr bool keyed_tile() {
@@ -136,11 +122,10 @@ tile_kernel(T *__restrict__ d, int32_t *__restrict__ P, int n, int64_t ld, int64
             close = idx == dix;
         }
     }
-    switch (mode) {
-    case 0: panel_coords(idx, b, nb - 1, bi, bj); break;
-    case 1: bulk_coords(idx, b, nb - 1, bi, bj); break;
-    default: edge_coords(idx, b, nb - 1, bi, bj); break;
-    }
+    if (mode == 0)
+        panel_coords(idx, b, nb - 1, bi, bj);
+    else
+        bulk_coords(idx, b, nb - 1, bi, bj);
     if constexpr (keyed_tile<T, S, BK, PRED, A>())
         product_tile_key<S, BK, TM, TN, VEC>(d, P, n, ld, ldp, bi, bj, b, smem);
     else
@@ -215,27 +200,54 @@ hipError_t tile64_launch(T *d, int n, int64_t ld, bool vec, int b, int nb, int m
     return hipGetLastError();
 }
 
-// Phase 3 for 128-wide tiles without predecessors and with 16-byte aligned
-// rows: the bulk tiles among the first nf full blocks (blockIdx.x enumerates
-// (nf-1)^2 of them, mf = nf - 1), slices copied into LDS directly
-// (bulk_tile_dma); four waves per SIMD.
+// Phase 3 for 128-wide tiles without predecessors: every bulk tile of the
+// stage (blockIdx.x enumerates (nb-1)^2), slices copied into LDS directly
+// (bulk_tile_dma): 16 bytes a lane where the rows are 16-byte aligned (VEC), 4
+// otherwise and for the tiles of a partial last block; four waves per SIMD.
+// Measured, fp32 n=6001 (unaligned, 46 full blocks and a partial one): 170 us
+// a stage, 8.0 ms a solve; with the bulk staged through registers and a
+// diagonal launch per stage 235 us, 11.1 ms.  n=8100 (aligned rows, a partial
+// last block): 15.9 ms; with a launch of its own for the edge tiles 18.1.
 //
-// With close_next (b + 1 < nf), the workgroup of tile (b+1, b+1) -- the next
-// stage's diagonal tile, whose stage-b value it alone computes -- also runs
-// that tile's closure, which replaces the next stage's phase-1 launch.  It
-// takes blockIdx 0 (swapped with the tile enumerated first) so that it is
+// With close_next the workgroup of tile (b+1, b+1) -- the next stage's
+// diagonal tile, whose stage-b value it alone computes -- also runs that
+// tile's closure, which replaces the next stage's phase-1 launch.  It takes
+// blockIdx 0 (swapped with the tile enumerated first) so that it is
 // dispatched early and its longer run overlaps the rest of the bulk.
-template <typename T, class A>
+template <typename T, bool VEC, class A>
 __global__ void __launch_bounds__(256, FW_BULK_DMA_WAVES)
-bulk_dma_kernel(T *__restrict__ d, int n, int64_t ld, int b, int mf, int close_next,
+bulk_dma_kernel(T *__restrict__ d, int n, int64_t ld, int b, int m, int close_next,
                 int32_t *flag, const T *acol) {
+    constexpr int S = 128, BK = 16;
+    __shared__ __align__(16) T A0[S * BK];
+    __shared__ __align__(16) T A1[S * BK];
+    __shared__ __align__(16) T B0[BK * S];
+    __shared__ __align__(16) T B1[BK * S];
+    __shared__ __align__(16) T X[kCloseExtra];
+    const BulkLds<T> lds = {A0, A1, B0, B1};
     if (given_up<A>(flag)) return;
     int idx = blockIdx.x;
-    const int dix = b * mf + b;  // enumeration index of tile (b+1, b+1)
+    const int dix = b * m + b;  // enumeration index of tile (b+1, b+1)
     if (close_next) idx = idx == 0 ? dix : idx == dix ? 0 : idx;
     int bi, bj;
-    bulk_coords(idx, b, mf, bi, bj);
-    bulk_tile_dma<T, A>(d, n, ld, bi, bj, b, close_next && idx == dix, flag, acol);
+    bulk_coords(idx, b, m, bi, bj);
+    const bool close = close_next && idx == dix;
+    const int last = n / S;  // blocks below it are full
+    if (bi < last && bj < last && b < last && ld < (int64_t(1) << 25))
+        bulk_tile_dma<T, VEC, false, A>(lds, d, n, ld, bi, bj, b, flag, acol);
+    else
+        bulk_tile_dma<T, VEC, true, A>(lds, d, n, ld, bi, bj, b, flag, acol);
+    if (!close) return;
+    // the next stage's diagonal tile: reread by the same workgroup (the
+    // barrier orders its stores before the loads) and closed in place; the
+    // product's LDS buffers are free by now
+    __syncthreads();
+    if constexpr (closure_in_blocks<T, S, false, A>())
+        closure_blocks<T, S, 8, 8, A, false>(d, n, ld, bi * S,
+                                             ClosureLds<T>{B0, B1, A0, A1, X, nullptr});
+    else if constexpr (VEC)  // bulk_closes: a tile inside the matrix
+        closure_tile<T, S, 8, false, A, true>(d, nullptr, n, ld, 0, bi * S,
+                                              reinterpret_cast<char *>(A0), flag);
 }
 
 // Phase 2 for 128-wide tiles without predecessors: each panel tile as four
@@ -645,8 +657,7 @@ hipError_t tile_t(int tile, T *d, int32_t *p, int n, int64_t ld, int64_t ldp, in
                 <<<grid, (128 / TMP) * (128 / TNP), 0, st>>>(d, p, n, ld, ldp, b, nb, mode,
                                                              close_next, flag, gate);
         } else {
-            tile_kernel<T, 128, 16, 8, 8, VEC, PRED, A><<<grid, 256, 0, st>>>(
-                d, p, n, ld, ldp, b, nb, mode, 0, flag, gate);
+            return hipErrorInvalidValue;  // panel_strip_kernel's, bulk_dma_kernel's
         }
         break;
     case 64:
@@ -665,16 +676,16 @@ hipError_t tile_t(int tile, T *d, int32_t *p, int n, int64_t ld, int64_t ldp, in
     return hipGetLastError();
 }
 
-// The bulk of stage b goes through bulk_dma_kernel: 128-wide tiles, no
-// predecessors, 16-byte aligned rows, a full k-block, and 32-bit per-lane
-// copy offsets (ld below 2^25).
-bool bulk_copy_path(int tile, bool vec, int n, int64_t ld, int b) {
-#if FW_BULK_DMA
-    return tile == 128 && vec && b < n / 128 && ld < (int64_t(1) << 25);
-#else
-    (void)tile, (void)vec, (void)n, (void)ld, (void)b;
-    return false;
-#endif
+// The bulk launch of stage b also closes the next diagonal tile: at tile 64;
+// at tile 128 with predecessors, and without them wherever the closure takes
+// the bulk workgroup's registers: in sub-blocks, or, on keys, a whole tile in
+// 16-byte pieces.
+bool bulk_closes(int sr, int tile, bool pred, bool vec, int n, int b) {
+    if (b + 1 >= (n + tile - 1) / tile) return false;
+    if (tile == 64) return !pred || sr == kMinPlus;
+    if (tile != 128) return false;
+    if (pred) return sr == kMinPlus;
+    return sr != kKey || (vec && b + 1 < n / 128);
 }
 
 template <typename T, class A, bool ALLOW_PRED>
@@ -690,12 +701,8 @@ hipError_t tile_dispatch(int tile, T *d, int32_t *p, int n, int64_t ld, int64_t 
     if (grid <= 0) return close_next ? hipErrorInvalidValue : hipSuccess;
     if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
     const bool vec = vec_ok(d, ld) && (p == nullptr || vec_ok(p, ldp));
-    // closing the next diagonal: tile 64 in any form, the copy path at 128
-    // without predecessors, the 128-wide predecessor kernel with them
-    if (close_next &&
-        (mode != 1 || b + 1 >= nb ||
-         (tile != 64 &&
-          (p ? (!ALLOW_PRED || tile != 128) : !bulk_copy_path(tile, vec, n, ld, b)))))
+    constexpr int kSr = A::kChecked ? kKey : kMinPlus;
+    if (close_next && (mode != 1 || !bulk_closes(kSr, tile, p != nullptr, vec, n, b)))
         return hipErrorInvalidValue;
     const int c = close_next ? 1 : 0;
     // the keyed 128-wide sweep's cleared column panel (in the solve's scratch)
@@ -717,35 +724,23 @@ hipError_t tile_dispatch(int tile, T *d, int32_t *p, int n, int64_t ld, int64_t 
                                             (unsigned)grid, st, flag, gate)
                    : tile64_launch<T, 1, A>(d, n, ld, vec, b, nb, mode, close_next,
                                             (unsigned)grid, st, flag, gate);
-#if FW_PANEL_STRIPS
-    if (mode == 0 && tile == 128) {
-        if (4 * grid > 0x7fffffffLL) return hipErrorInvalidValue;
-        if (vec)
-            panel_strip_kernel<T, true, A><<<(unsigned)(4 * grid), 256, 0, st>>>(d, n, ld, b, nb,
-                                                                                flag, acol);
-        else
-            panel_strip_kernel<T, false, A><<<(unsigned)(4 * grid), 256, 0, st>>>(
-                d, n, ld, b, nb, flag, acol);
-        return hipGetLastError();
-    }
-#endif
-    // Stage with a full k-block: full tiles through bulk_dma_kernel, the
-    // tiles of a partial last block (if any) through tile_kernel mode 4.
-    const int nf = n / 128;
-    // the keyed copy path reads the cleared column panel the strips write
-    if (mode == 1 && bulk_copy_path(tile, vec, n, ld, b) && (!A::kChecked || FW_PANEL_STRIPS)) {
-        const int64_t mf = nf - 1;
-        if (close_next && b + 1 >= nf) return hipErrorInvalidValue;
-        if (mf > 0) {
-            bulk_dma_kernel<T, A><<<(unsigned)(mf * mf), 256, 0, st>>>(
-                d, n, ld, b, (int)mf, close_next ? 1 : 0, flag, acol);
-            const hipError_t e = hipGetLastError();
-            if (e != hipSuccess) return e;
+    if (tile == 128) {
+        if (mode == 0) {
+            if (4 * grid > 0x7fffffffLL) return hipErrorInvalidValue;
+            if (vec)
+                panel_strip_kernel<T, true, A><<<(unsigned)(4 * grid), 256, 0, st>>>(
+                    d, n, ld, b, nb, flag, acol);
+            else
+                panel_strip_kernel<T, false, A><<<(unsigned)(4 * grid), 256, 0, st>>>(
+                    d, n, ld, b, nb, flag, acol);
+        } else if (vec) {
+            bulk_dma_kernel<T, true, A><<<(unsigned)grid, 256, 0, st>>>(d, n, ld, b, (int)m, c,
+                                                                       flag, acol);
+        } else {
+            bulk_dma_kernel<T, false, A><<<(unsigned)grid, 256, 0, st>>>(d, n, ld, b, (int)m, c,
+                                                                        flag, acol);
         }
-        if (nf < nb)
-            return tile_t<T, true, false, A>(tile, d, p, n, ld, ldp, b, nb, 2,
-                                             (unsigned)(2 * m - 1), st, 0, flag, nullptr);
-        return hipSuccess;
+        return hipGetLastError();
     }
     if (close_next) return hipErrorInvalidValue;  // every closing form is handled above
     return vec ? tile_t<T, true, false, A>(tile, d, p, n, ld, ldp, b, nb, mode, (unsigned)grid, st,
@@ -815,15 +810,7 @@ hipError_t launch_panels(int dtype, int sr, int tile, void *d, int32_t *p, int n
 
 bool bulk_closes_next_diag(int sr, int tile, const void *d, const int32_t *p, int n, int64_t ld,
                            int b) {
-#if FW_FUSE_DIAG
-    if (tile == 64) return (!p || sr == kMinPlus) && b + 1 < (n + 63) / 64;
-    if (p) return sr == kMinPlus && tile == 128 && b + 1 < (n + 127) / 128;
-    if (sr == kKey && !FW_PANEL_STRIPS) return false;
-    return bulk_copy_path(tile, vec_ok(d, ld), n, ld, b) && b + 1 < n / 128;
-#else
-    (void)sr, (void)tile, (void)d, (void)p, (void)n, (void)ld, (void)b;
-    return false;
-#endif
+    return bulk_closes(sr, tile, p != nullptr, vec_ok(d, ld), n, b);
 }
 
 hipError_t launch_bulk(int dtype, int sr, int tile, void *d, int32_t *p, int n, int64_t ld,

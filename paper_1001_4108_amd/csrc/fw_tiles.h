@@ -200,6 +200,12 @@ __device__ __forceinline__ int32_t final_pred(int i, int j, T v, int32_t p) {
 }
 
 template <typename T> struct Vec4 { typedef T type __attribute__((ext_vector_type(4))); };
+// Four consecutive values at any 4-byte address: gfx950's 16-byte global loads
+// and stores need no more.
+template <typename T>
+struct Vec4u {
+    typedef T type __attribute__((ext_vector_type(4), aligned(4)));
+};
 
 // Load E consecutive elements of one matrix row starting at column `col`;
 // out-of-range elements read as `fill`.
@@ -219,8 +225,20 @@ __device__ __forceinline__ void row_load(T (&v)[E], const T *__restrict__ base, 
         }
     } else if (full) {
         const T *src = base + (int64_t)row * ld + col;
+        if constexpr (E % 4 == 0) {
 #pragma unroll
-        for (int e = 0; e < E; ++e) v[e] = src[e];
+            for (int e = 0; e < E; e += 4) {
+                const typename Vec4u<T>::type x =
+                    *reinterpret_cast<const typename Vec4u<T>::type *>(src + e);
+                v[e] = x[0];
+                v[e + 1] = x[1];
+                v[e + 2] = x[2];
+                v[e + 3] = x[3];
+            }
+        } else {
+#pragma unroll
+            for (int e = 0; e < E; ++e) v[e] = src[e];
+        }
     } else {
         const bool rok = row < n;
         const T *src = base + (rok ? (int64_t)row * ld : 0);
@@ -245,8 +263,20 @@ __device__ __forceinline__ void row_store(const T (&v)[E], T *__restrict__ base,
         }
     } else if (full) {
         T *dst = base + (int64_t)row * ld + col;
+        if constexpr (E % 4 == 0) {
 #pragma unroll
-        for (int e = 0; e < E; ++e) dst[e] = v[e];
+            for (int e = 0; e < E; e += 4) {
+                typename Vec4u<T>::type x;
+                x[0] = v[e];
+                x[1] = v[e + 1];
+                x[2] = v[e + 2];
+                x[3] = v[e + 3];
+                *reinterpret_cast<typename Vec4u<T>::type *>(dst + e) = x;
+            }
+        } else {
+#pragma unroll
+            for (int e = 0; e < E; ++e) dst[e] = v[e];
+        }
     } else if (row < n) {
         T *dst = base + (int64_t)row * ld;
 #pragma unroll
@@ -498,7 +528,7 @@ struct ClosureLds {
     T *e;      // 8 x S, AHEAD only
 };
 
-template <typename T, int S, int TM, int TN, class A, bool FULL, bool AHEAD = false>
+template <typename T, int S, int TM, int TN, class A, bool AHEAD>
 __device__ __forceinline__ void closure_blocks(T *__restrict__ d, int n, int64_t ld, int base,
                                                const ClosureLds<T> &lds) {
     static_assert(!A::kChecked, "range-checked keys take closure_tile");
@@ -517,9 +547,8 @@ __device__ __forceinline__ void closure_blocks(T *__restrict__ d, int n, int64_t
     if (ahead) __builtin_amdgcn_s_setprio(3);
     int tx = threadIdx.x % G, ty = threadIdx.x / G;
     const int lane = threadIdx.x & 63, g = lane >> 4, cq = lane & 7;
-    // a tile inside the matrix with 16-byte aligned rows (FULL: the caller
-    // guarantees it) moves in 16-byte pieces
-    const bool full = FULL || (base + S <= n && (uintptr_t)d % 16 == 0 && ld % 4 == 0);
+    // a tile inside the matrix moves in 16-byte pieces (at any alignment)
+    const bool full = base + S <= n;
     T c[TM][TN], D[2];
     if (!ahead) {
 #pragma unroll
@@ -527,7 +556,7 @@ __device__ __forceinline__ void closure_blocks(T *__restrict__ d, int n, int64_t
 #pragma unroll
             for (int h = 0; h < TN / CW; ++h) {
                 T v[CW];
-                row_load<T, CW, CW == 4>(v, d, base + ty * TM + r, base + h * CW * G + tx * CW, n,
+                row_load<T, CW, false>(v, d, base + ty * TM + r, base + h * CW * G + tx * CW, n,
                                          ld, full, A::inf());
 #pragma unroll
                 for (int e = 0; e < CW; ++e) c[r][CW * h + e] = v[e];
@@ -699,7 +728,7 @@ __device__ __forceinline__ void closure_blocks(T *__restrict__ d, int n, int64_t
                 T v[CW];
 #pragma unroll
                 for (int e = 0; e < CW; ++e) v[e] = c[r][CW * h + e];
-                row_store<T, CW, CW == 4>(v, d, base + sty * TM + r, base + h * CW * G + stx * CW,
+                row_store<T, CW, false>(v, d, base + sty * TM + r, base + h * CW * G + stx * CW,
                                           n, ld, full);
             }
     }
@@ -751,7 +780,7 @@ __device__ __forceinline__ void closure_tile_any(T *__restrict__ d, int32_t *__r
         T *b = reinterpret_cast<T *>(smem);
         constexpr int W = kClosureK * S;
         const ClosureLds<T> lds = {b, b + W, b + 2 * W, b + 3 * W, b + 4 * W, b + 4 * W + kCloseExtra};
-        closure_blocks<T, S, TM, TN, A, false, AHEAD>(d, n, ld, base, lds);
+        closure_blocks<T, S, TM, TN, A, AHEAD>(d, n, ld, base, lds);
     } else {
         static_assert(TM == TN, "closure_tile has square sub-tiles");
         closure_tile<T, S, TM, PRED, A>(d, P, n, ld, ldp, base, smem, flag);
@@ -931,6 +960,7 @@ __device__ __forceinline__ void product_tile_whole(T *__restrict__ d, int n, int
                                                    int32_t *flag = nullptr) {
     constexpr int S = 64, TM = 4, P = 4 / HALVES;  // P: 16-row groups a thread stages
     typedef typename Vec4<T>::type V4;
+    using V4g = std::conditional_t<VEC, V4, typename Vec4u<T>::type>;  // in the matrix
     T *As = reinterpret_cast<T *>(smem), *Bs = As + S * S;
     const int half = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8);
     const int tid = threadIdx.x & 255, tx = tid & 15, ty = tid >> 4;
@@ -940,17 +970,17 @@ __device__ __forceinline__ void product_tile_whole(T *__restrict__ d, int n, int
     if (half < HALVES) {
         V4 ra[P], rb[P];
         const int sr = half * P * 16 + ty;  // first row staged
-        if (VEC && full) {
+        if (full) {
 #pragma unroll
             for (int i = 0; i < P; ++i) {
-                ra[i] = *reinterpret_cast<const V4 *>(d + (row0 + sr + i * 16) * ld + k0 + tx * 4);
-                rb[i] = *reinterpret_cast<const V4 *>(d + (k0 + sr + i * 16) * ld + col0 + tx * 4);
+                ra[i] = *reinterpret_cast<const V4g *>(d + (row0 + sr + i * 16) * ld + k0 + tx * 4);
+                rb[i] = *reinterpret_cast<const V4g *>(d + (k0 + sr + i * 16) * ld + col0 + tx * 4);
             }
             if (half == 0) {
 #pragma unroll
                 for (int i = 0; i < TM; ++i)
-                    acc[i] = *reinterpret_cast<const V4 *>(d + (row0 + ty * TM + i) * ld + col0 +
-                                                           tx * 4);
+                    acc[i] = *reinterpret_cast<const V4g *>(d + (row0 + ty * TM + i) * ld + col0 +
+                                                            tx * 4);
             }
         } else {
             // addresses clamped into the matrix, so that every load is issued
@@ -1060,11 +1090,10 @@ __device__ __forceinline__ void product_tile_whole(T *__restrict__ d, int n, int
 }
 
 // ---------------------------------------------------------------------------
-// bulk_tile_dma: the 128 x 128 tile update of product_tile (no predecessors)
-// for a tile that lies inside the matrix with a full k-block, the k-slices
-// moved from global memory straight into LDS by gfx950's global->LDS dwordx4
-// loads instead of through registers.  A thread keeps only its 8 x 8 cells
-// and one k-pair of operands, so four waves fit on a SIMD where the
+// bulk_tile_dma: the 128 x 128 tile update of product_tile (no predecessors),
+// the k-slices moved from global memory straight into LDS by gfx950's
+// global->LDS loads instead of through registers.  A thread keeps only its
+// 8 x 8 cells and one k-pair of operands, so four waves fit on a SIMD where the
 // register-staged form fits three, and the copy costs no LDS store
 // instructions.
 //
@@ -1075,11 +1104,21 @@ __device__ __forceinline__ void product_tile_whole(T *__restrict__ d, int n, int
 //            position c ^ ((r / 8) % 4), so that the 4 rows one wave reads
 //            together fall in different banks;
 //   B slice: 16 k x 128 columns, as in global memory.
-// Requirements on the caller: 256 threads, 16-byte aligned rows (base
-// aligned, ld % 4 == 0), tile and k-block inside the matrix.  Per cell the
+// Three forms of the copy, the layout the same:
+//   VEC, EDGE false: 16 bytes a lane (16-byte aligned rows), the tile and the
+//            k-block inside the matrix;
+//   VEC false:       4 bytes a lane, for rows of any alignment: 16 copies a
+//            wave and slice instead of 4, which the slice's 1536 vector
+//            instructions hide;
+//   EDGE true:       4 bytes a lane, the tile or the k-block reaching past
+//            the last vertex: every source is clamped to row and column
+//            n - 1, the k loop stops at the last vertex, and cells outside
+//            the matrix are neither loaded nor stored (they compute values
+//            from clamped operands that go nowhere).
+// Requirements on the caller: 256 threads; without EDGE ld < 2^25 (32-bit
+// offsets within a tile).  Per cell the
 // same candidates are formed, one add each, as in product_tile, hence the
-// same bits.  With `close` (uniform per workgroup; the tile is (b+1, b+1))
-// the tile's closure for stage b+1 follows the store.
+// same bits.
 // ---------------------------------------------------------------------------
 typedef __attribute__((address_space(3))) void lds_void_t;
 
@@ -1094,21 +1133,25 @@ struct Pair<int32_t> {
     using type = int2;
 };
 
+// LDS of bulk_tile_dma (2048 values each), shared by the forms a kernel holds.
+template <typename T>
+struct BulkLds {
+    T *A0, *A1, *B0, *B1;
+};
+
 // With the keyed policy the A slices come from `acol` (the stage's column
 // panel with the hop fields cleared, 128 values per row, written by the
 // panel launch), so the k loop adds without clearing.
-template <typename T, class A = Ar<T>>
-__device__ __forceinline__ void bulk_tile_dma(T *__restrict__ d, int n, int64_t ld, int bi,
-                                              int bj, int b, bool close, int32_t *flag = nullptr,
+template <typename T, bool VEC, bool EDGE, class A = Ar<T>>
+__device__ __forceinline__ void bulk_tile_dma(const BulkLds<T> &lds, T *__restrict__ d, int n,
+                                              int64_t ld, int bi, int bj, int b,
+                                              int32_t *flag = nullptr,
                                               const T *__restrict__ acol = nullptr) {
     static_assert(sizeof(T) == 4, "32-bit values");
     constexpr int S = 128, BK = 16, TM = 8, NS = S / BK;
     static_assert(NS % 2 == 0, "slices alternate between two buffers");
-    __shared__ __align__(16) T A0[S * BK];
-    __shared__ __align__(16) T A1[S * BK];
-    __shared__ __align__(16) T B0[BK * S];
-    __shared__ __align__(16) T B1[BK * S];
-    __shared__ __align__(16) T X[kCloseExtra];  // the closure's
+    T *A0 = lds.A0, *A1 = lds.A1, *B0 = lds.B0, *B1 = lds.B1;
+    using V4 = std::conditional_t<VEC, typename Vec4<T>::type, typename Vec4u<T>::type>;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1124,42 +1167,96 @@ __device__ __forceinline__ void bulk_tile_dma(T *__restrict__ d, int n, int64_t 
         T *row = d + (row0 + ty * TM + i) * ld + col0 + tx * 4;
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            const typename Vec4<T>::type x =
-                *reinterpret_cast<const typename Vec4<T>::type *>(row + h * 64);
-            acc[i][4 * h] = x[0];
-            acc[i][4 * h + 1] = x[1];
-            acc[i][4 * h + 2] = x[2];
-            acc[i][4 * h + 3] = x[3];
+            if constexpr (EDGE) {
+                const bool rok = row0 + ty * TM + i < n;
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    acc[i][4 * h + e] =
+                        rok && col0 + tx * 4 + h * 64 + e < n ? row[h * 64 + e] : A::inf();
+            } else {
+                const V4 x = *reinterpret_cast<const V4 *>(row + h * 64);
+                acc[i][4 * h] = x[0];
+                acc[i][4 * h + 1] = x[1];
+                acc[i][4 * h + 2] = x[2];
+                acc[i][4 * h + 3] = x[3];
+            }
         }
     }
 
-    // Copy sources: wave-uniform bases plus 32-bit per-lane offsets.  The
-    // wave copies A rows 32*wave + lane/4 (and +16) and B k-rows
-    // 4*wave + lane/32 (and +2) of each slice.
+    // Copy sources: wave-uniform bases plus 32-bit per-lane offsets.  A wave
+    // copies A rows 32*wave .. + 31 and B k-rows 4*wave .. + 3 of each slice.
     const int64_t lda = A::kChecked ? (int64_t)S : ld;
-    const T *a_base = A::kChecked ? acol + (row0 + wave * 32) * S
-                                  : d + (row0 + wave * 32) * ld + k0;
-    const T *b_base = d + (k0 + wave * 4) * ld + col0;
+    const T *a_tile = A::kChecked ? acol + row0 * S : d + row0 * ld + k0;
+    const T *b_tile = d + k0 * ld + col0;
+    const T *a_base = a_tile + wave * 32 * lda, *b_base = b_tile + wave * 4 * ld;
     const int ar = wave * 32 + (lane >> 2);
     const uint32_t a_off0 = (uint32_t)((lane >> 2) * lda) + (((lane & 3) ^ ((ar >> 3) & 3)) << 2);
     const uint32_t a_off1 =
         (uint32_t)(((lane >> 2) + 16) * lda) + (((lane & 3) ^ (((ar + 16) >> 3) & 3)) << 2);
     const uint32_t b_off0 = (uint32_t)((lane >> 5) * ld) + ((lane & 31) << 2);
     const uint32_t b_off1 = b_off0 + (uint32_t)(2 * ld);
+    const uint32_t a_lane = (uint32_t)((lane >> 4) * lda) + (lane & 3);
+    const int last_r = (int)(n - 1 - row0), last_c = (int)(n - 1 - col0), last_k = (int)(n - 1 - k0);
     auto issue = [&](int s, T *Ad, T *Bd) {
-        const T *as = a_base + s * BK;
-        const T *bs = b_base + (int64_t)s * BK * ld;
         T *a = Ad + wave * 32 * BK;
         T *bb = Bd + wave * 4 * S;
-        __builtin_amdgcn_global_load_lds(as + a_off0, (lds_void_t *)a, 16, 0, 0);
-        __builtin_amdgcn_global_load_lds(as + a_off1, (lds_void_t *)(a + 16 * BK), 16, 0, 0);
-        __builtin_amdgcn_global_load_lds(bs + b_off0, (lds_void_t *)bb, 16, 0, 0);
-        __builtin_amdgcn_global_load_lds(bs + b_off1, (lds_void_t *)(bb + 2 * S), 16, 0, 0);
+        if constexpr (EDGE) {
+            // addresses formed anew for each slice from an opaque copy of the
+            // lane (no instruction is emitted), not kept through the k loop
+            int el = lane;
+            asm volatile("" : "+v"(el));
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                // lane: row el / 16 of four, position el % 16 of the row
+                const int r = min(wave * 32 + 4 * i + (el >> 4), last_r);
+                const int c = ((((el >> 2) & 3) ^ (i >> 1)) << 2) + (el & 3);
+                __builtin_amdgcn_global_load_lds(a_tile + r * lda + min(s * BK + c, last_k),
+                                                 (lds_void_t *)(a + i * 64), 4, 0, 0);
+            }
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int k = min(s * BK + wave * 4 + (i >> 1), last_k);
+                __builtin_amdgcn_global_load_lds(
+                    b_tile + (int64_t)k * ld + min((i & 1) * 64 + el, last_c),
+                    (lds_void_t *)(bb + i * 64), 4, 0, 0);
+            }
+        } else if constexpr (VEC) {
+            const T *as = a_base + s * BK;
+            const T *bs = b_base + (int64_t)s * BK * ld;
+            __builtin_amdgcn_global_load_lds(as + a_off0, (lds_void_t *)a, 16, 0, 0);
+            __builtin_amdgcn_global_load_lds(as + a_off1, (lds_void_t *)(a + 16 * BK), 16, 0, 0);
+            __builtin_amdgcn_global_load_lds(bs + b_off0, (lds_void_t *)bb, 16, 0, 0);
+            __builtin_amdgcn_global_load_lds(bs + b_off1, (lds_void_t *)(bb + 2 * S), 16, 0, 0);
+        } else {
+            const T *as = a_base + s * BK;
+            const T *bs = b_base + (int64_t)s * BK * ld;
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                __builtin_amdgcn_global_load_lds(
+                    as + 4 * i * lda + (a_lane + ((((lane >> 2) & 3) ^ (i >> 1)) << 2)),
+                    (lds_void_t *)(a + i * 64), 4, 0, 0);
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                __builtin_amdgcn_global_load_lds(bs + (i >> 1) * ld + (i & 1) * 64 + lane,
+                                                 (lds_void_t *)(bb + i * 64), 4, 0, 0);
+        }
     };
-    auto compute = [&](const T *Ab, const T *Bb) {
+    // EDGE: a wave whose 32 rows all lie beyond the matrix skips the
+    // arithmetic (it still copies its share and meets every barrier)
+    const bool idle = EDGE && wave * 32 > last_r;
+    // kl: the slice's k inside the matrix
+    auto compute = [&](const T *Ab, const T *Bb, int kl) {
+        if (EDGE && idle) return;
+        auto add = [](T x, T y) {
+            if constexpr (A::kChecked)
+                return A::add_cleared(x, y);
+            else
+                return A::add(x, y);
+        };
+        const int kpairs = EDGE ? kl & ~1 : BK;
         // one k-pair per iteration (see product_tile)
 #pragma unroll 1
-        for (int kk = 0; kk < BK; kk += 2) {
+        for (int kk = 0; kk < kpairs; kk += 2) {
             const int aoff = ty * (TM * BK) + (((kk >> 2) ^ (ty & 3)) << 2) + (kk & 3);
             T a0[TM], a1[TM], b0[TM], b1[TM];
 #pragma unroll
@@ -1178,15 +1275,21 @@ __device__ __forceinline__ void bulk_tile_dma(T *__restrict__ d, int n, int64_t 
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
-                for (int j = 0; j < TM; ++j) {
-                    if constexpr (A::kChecked)
-                        acc[i][j] = A::min3(acc[i][j], A::add_cleared(a0[i], b0[j]),
-                                            A::add_cleared(a1[i], b1[j]));
-                    else
-                        acc[i][j] = A::min3(acc[i][j], A::add(a0[i], b0[j]), A::add(a1[i], b1[j]));
-                }
+                for (int j = 0; j < TM; ++j)
+                    acc[i][j] = A::min3(acc[i][j], add(a0[i], b0[j]), add(a1[i], b1[j]));
+        }
+        if (EDGE && (kl & 1)) {  // the last k alone
+            const int kk = kl - 1;
+            const int aoff = ty * (TM * BK) + (((kk >> 2) ^ (ty & 3)) << 2) + (kk & 3);
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TM; ++j)
+                    acc[i][j] = A::min2(acc[i][j], add(Ab[aoff + i * BK],
+                                                       Bb[kk * S + (j >> 2) * 64 + tx * 4 + (j & 3)]));
         }
     };
+    auto slice_k = [&](int s) { return EDGE ? max(0, min(BK, last_k + 1 - s * BK)) : BK; };
 
     // vmcnt(0): this wave's copies (and its C loads) have landed; the
     // barrier after it makes every wave's copies visible and guarantees that
@@ -1198,11 +1301,11 @@ __device__ __forceinline__ void bulk_tile_dma(T *__restrict__ d, int n, int64_t 
         __builtin_amdgcn_s_waitcnt(kWaitVm0);
         __syncthreads();
         issue(s + 1, A1, B1);
-        compute(A0, B0);
+        compute(A0, B0, slice_k(s));
         __builtin_amdgcn_s_waitcnt(kWaitVm0);
         __syncthreads();
         if (s + 2 < NS) issue(s + 2, A0, B0);
-        compute(A1, B1);
+        compute(A1, B1, slice_k(s + 1));
     }
 
     // store addresses recomputed from opaque copies of the thread ids (no
@@ -1215,7 +1318,13 @@ __device__ __forceinline__ void bulk_tile_dma(T *__restrict__ d, int n, int64_t 
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
-            for (int j = 0; j < TM; ++j) acc[i][j] = settle<A>(acc[i][j], bad);
+            for (int j = 0; j < TM; ++j) {
+                // a cell outside the matrix checks nothing
+                if (EDGE && (row0 + sty * TM + i >= n ||
+                             col0 + stx * 4 + (j >> 2) * 64 + (j & 3) >= n))
+                    acc[i][j] = A::inf();
+                acc[i][j] = settle<A>(acc[i][j], bad);
+            }
         raise_flag<A>(flag, bad);
     }
 #pragma unroll
@@ -1223,25 +1332,20 @@ __device__ __forceinline__ void bulk_tile_dma(T *__restrict__ d, int n, int64_t 
         T *row = d + (row0 + sty * TM + i) * ld + col0 + stx * 4;
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            typename Vec4<T>::type x;
-            x[0] = acc[i][4 * h];
-            x[1] = acc[i][4 * h + 1];
-            x[2] = acc[i][4 * h + 2];
-            x[3] = acc[i][4 * h + 3];
-            *reinterpret_cast<typename Vec4<T>::type *>(row + h * 64) = x;
+            if constexpr (EDGE) {
+                const bool rok = row0 + sty * TM + i < n;
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (rok && col0 + stx * 4 + h * 64 + e < n) row[h * 64 + e] = acc[i][4 * h + e];
+            } else {
+                V4 x;
+                x[0] = acc[i][4 * h];
+                x[1] = acc[i][4 * h + 1];
+                x[2] = acc[i][4 * h + 2];
+                x[3] = acc[i][4 * h + 3];
+                *reinterpret_cast<V4 *>(row + h * 64) = x;
+            }
         }
-    }
-    if (close) {
-        // the next stage's diagonal tile: reread by the same workgroup (the
-        // barrier orders its stores before the loads) and closed in place;
-        // the product's LDS buffers are free by now
-        __syncthreads();
-        if constexpr (closure_in_blocks<T, S, false, A>())
-            closure_blocks<T, S, TM, TM, A, true>(d, n, ld, (int)row0,
-                                                  ClosureLds<T>{B0, B1, A0, A1, X, nullptr});
-        else
-            closure_tile<T, S, TM, false, A, true>(d, nullptr, n, ld, 0, (int)row0,
-                                                   reinterpret_cast<char *>(A0), flag);
     }
 }
 
@@ -1509,21 +1613,6 @@ __device__ __forceinline__ void bulk_coords(int idx, int b, int m, int &bi, int 
     const int q = idx / m, r = idx - q * m;
     bi = q < b ? q : q + 1;
     bj = r < b ? r : r + 1;
-}
-
-// Bulk tiles of stage b (b < nb - 1) that lie in the last block row or
-// column, nb - 1 being a partial block: 2m - 1 of them (m = nb - 1).  The
-// other bulk tiles are the (m - 1)^2 of bulk_coords over the first nb - 1
-// blocks.
-__device__ __forceinline__ void edge_coords(int idx, int b, int m, int &bi, int &bj) {
-    if (idx < m) {
-        bi = m;
-        bj = idx < b ? idx : idx + 1;
-    } else {
-        idx -= m;
-        bi = idx < b ? idx : idx + 1;
-        bj = m;
-    }
 }
 
 }  // namespace fw
