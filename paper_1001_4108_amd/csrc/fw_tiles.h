@@ -285,6 +285,56 @@ __device__ __forceinline__ void row_store(const T (&v)[E], T *__restrict__ base,
     }
 }
 
+// A policy's "add" for a first operand that first() has prepared: the keyed
+// policy clears the hop field once per operand instead of once per sum.
+template <class A, typename T>
+__device__ __forceinline__ T first(T a) {
+    if constexpr (A::kChecked)
+        return A::clear_hop(a);
+    else
+        return a;
+}
+template <class A, typename T>
+__device__ __forceinline__ T add_first(T a, T b) {
+    if constexpr (A::kChecked)
+        return A::add_cleared(a, b);
+    else
+        return A::add(a, b);
+}
+
+// Four cells of a product over a k-pair: c_e <- min3(c_e, a0 x b0_e, a1 x b1_e)
+// (a0, a1 prepared by first()).
+// Integer min-plus, written out: what bounds the int32 and keyed products is
+// how the adds of one wave share the SIMD with the minima of the others, and
+// that hangs on the order of issue.  Left to the compiler the two sums of every
+// cell go through the same two registers, and the loop issues 56 lanes per
+// clock per CU of a possible 107; with two registers of its own per cell and a
+// one-cycle gap before each minimum it issues 69 (n=8192 int32: 24.4 -> 19.9
+// ms, with predecessors 25.6 -> 21.1; without the gap 22.7, with the eight adds
+// first 21.6, with a gap of three cycles 22.5).  fp32 is fastest as the compiler
+// orders it (n=16384 110 ms against 116-139 in these forms).
+template <class A, typename T>
+__device__ __forceinline__ void update4(T (&c)[4], T a0, T a1, const T *b0, const T *b1) {
+    if constexpr (std::is_same<A, Ar<int32_t>>::value || A::kChecked) {
+        int32_t s[4], t[4];
+#define FW_CELL(i)                                                                   \
+    "v_add_u32 %[s" #i "], %[p" #i "], %[a]\n\t"                                     \
+    "v_add_u32 %[t" #i "], %[q" #i "], %[b]\n\t"                                     \
+    "s_nop 0\n\t"                                                                    \
+    "v_min3_i32 %[c" #i "], %[c" #i "], %[s" #i "], %[t" #i "]\n\t"
+        asm(FW_CELL(0) FW_CELL(1) FW_CELL(2) FW_CELL(3)
+            : [c0] "+v"(c[0]), [c1] "+v"(c[1]), [c2] "+v"(c[2]), [c3] "+v"(c[3]), [s0] "=&v"(s[0]),
+              [s1] "=&v"(s[1]), [s2] "=&v"(s[2]), [s3] "=&v"(s[3]), [t0] "=&v"(t[0]),
+              [t1] "=&v"(t[1]), [t2] "=&v"(t[2]), [t3] "=&v"(t[3])
+            : [a] "v"(a0), [b] "v"(a1), [p0] "v"(b0[0]), [p1] "v"(b0[1]), [p2] "v"(b0[2]),
+              [p3] "v"(b0[3]), [q0] "v"(b1[0]), [q1] "v"(b1[1]), [q2] "v"(b1[2]), [q3] "v"(b1[3]));
+#undef FW_CELL
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) c[e] = A::min3(c[e], A::add(a0, b0[e]), A::add(a1, b1[e]));
+    }
+}
+
 // ---------------------------------------------------------------------------
 // closure_tile: s dependent k-steps on the tile with origin (base, base).
 //
@@ -1013,6 +1063,10 @@ __device__ __forceinline__ void product_tile_whole(T *__restrict__ d, int n, int
 #pragma unroll
         for (int i = 0; i < P; ++i) {
             const int r = sr + i * 16;
+            if constexpr (A::kChecked) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) ra[i][e] = first<A, T>(ra[i][e]);
+            }
             *reinterpret_cast<V4 *>(As + r * S + (tx ^ (r >> 2)) * 4) = ra[i];
             *reinterpret_cast<V4 *>(Bs + r * S + tx * 4) = rb[i];
         }
@@ -1035,13 +1089,17 @@ __device__ __forceinline__ void product_tile_whole(T *__restrict__ d, int n, int
         };
         auto apply = [&](V4(&x)[TM], V4(&y)[4]) {
 #pragma unroll
-            for (int e = 0; e < 4; e += 2)
+            for (int e = 0; e < 4; e += 2) {
+                const T b0[4] = {y[e][0], y[e][1], y[e][2], y[e][3]};
+                const T b1[4] = {y[e + 1][0], y[e + 1][1], y[e + 1][2], y[e + 1][3]};
 #pragma unroll
-                for (int i = 0; i < TM; ++i)
+                for (int i = 0; i < TM; ++i) {
+                    T c[4] = {acc[i][0], acc[i][1], acc[i][2], acc[i][3]};
+                    update4<A>(c, (T)x[i][e], (T)x[i][e + 1], b0, b1);
 #pragma unroll
-                    for (int j = 0; j < TM; ++j)
-                        acc[i][j] = A::min3(acc[i][j], A::add(x[i][e], y[e][j]),
-                                            A::add(x[i][e + 1], y[e + 1][j]));
+                    for (int j = 0; j < TM; ++j) acc[i][j] = c[j];
+                }
+            }
             __builtin_amdgcn_sched_barrier(0);
         };
         read(s0, a[0], bb[0]);
@@ -1161,7 +1219,7 @@ __device__ __forceinline__ void bulk_tile_dma(const BulkLds<T> &lds, T *__restri
     // thread (tx, ty) owns rows 8*ty .. 8*ty + 7 and the two 4-column groups
     // starting at 4*tx and 64 + 4*tx: the 16 column groups a B read touches
     // are contiguous, so the read has no bank conflicts
-    T acc[TM][TM];
+    T acc[TM][2][4];
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
         T *row = d + (row0 + ty * TM + i) * ld + col0 + tx * 4;
@@ -1171,14 +1229,14 @@ __device__ __forceinline__ void bulk_tile_dma(const BulkLds<T> &lds, T *__restri
                 const bool rok = row0 + ty * TM + i < n;
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
-                    acc[i][4 * h + e] =
+                    acc[i][h][e] =
                         rok && col0 + tx * 4 + h * 64 + e < n ? row[h * 64 + e] : A::inf();
             } else {
                 const V4 x = *reinterpret_cast<const V4 *>(row + h * 64);
-                acc[i][4 * h] = x[0];
-                acc[i][4 * h + 1] = x[1];
-                acc[i][4 * h + 2] = x[2];
-                acc[i][4 * h + 3] = x[3];
+                acc[i][h][0] = x[0];
+                acc[i][h][1] = x[1];
+                acc[i][h][2] = x[2];
+                acc[i][h][3] = x[3];
             }
         }
     }
@@ -1247,12 +1305,6 @@ __device__ __forceinline__ void bulk_tile_dma(const BulkLds<T> &lds, T *__restri
     // kl: the slice's k inside the matrix
     auto compute = [&](const T *Ab, const T *Bb, int kl) {
         if (EDGE && idle) return;
-        auto add = [](T x, T y) {
-            if constexpr (A::kChecked)
-                return A::add_cleared(x, y);
-            else
-                return A::add(x, y);
-        };
         const int kpairs = EDGE ? kl & ~1 : BK;
         // one k-pair per iteration (see product_tile)
 #pragma unroll 1
@@ -1275,8 +1327,8 @@ __device__ __forceinline__ void bulk_tile_dma(const BulkLds<T> &lds, T *__restri
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
-                for (int j = 0; j < TM; ++j)
-                    acc[i][j] = A::min3(acc[i][j], add(a0[i], b0[j]), add(a1[i], b1[j]));
+                for (int h = 0; h < 2; ++h)
+                    update4<A>(acc[i][h], a0[i], a1[i], &b0[4 * h], &b1[4 * h]);
         }
         if (EDGE && (kl & 1)) {  // the last k alone
             const int kk = kl - 1;
@@ -1285,8 +1337,10 @@ __device__ __forceinline__ void bulk_tile_dma(const BulkLds<T> &lds, T *__restri
             for (int i = 0; i < TM; ++i)
 #pragma unroll
                 for (int j = 0; j < TM; ++j)
-                    acc[i][j] = A::min2(acc[i][j], add(Ab[aoff + i * BK],
-                                                       Bb[kk * S + (j >> 2) * 64 + tx * 4 + (j & 3)]));
+                    acc[i][j >> 2][j & 3] =
+                        A::min2(acc[i][j >> 2][j & 3],
+                                add_first<A>(Ab[aoff + i * BK],
+                                             Bb[kk * S + (j >> 2) * 64 + tx * 4 + (j & 3)]));
         }
     };
     auto slice_k = [&](int s) { return EDGE ? max(0, min(BK, last_k + 1 - s * BK)) : BK; };
@@ -1320,10 +1374,11 @@ __device__ __forceinline__ void bulk_tile_dma(const BulkLds<T> &lds, T *__restri
 #pragma unroll
             for (int j = 0; j < TM; ++j) {
                 // a cell outside the matrix checks nothing
+                T &c = acc[i][j >> 2][j & 3];
                 if (EDGE && (row0 + sty * TM + i >= n ||
                              col0 + stx * 4 + (j >> 2) * 64 + (j & 3) >= n))
-                    acc[i][j] = A::inf();
-                acc[i][j] = settle<A>(acc[i][j], bad);
+                    c = A::inf();
+                c = settle<A>(c, bad);
             }
         raise_flag<A>(flag, bad);
     }
@@ -1336,13 +1391,13 @@ __device__ __forceinline__ void bulk_tile_dma(const BulkLds<T> &lds, T *__restri
                 const bool rok = row0 + sty * TM + i < n;
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
-                    if (rok && col0 + stx * 4 + h * 64 + e < n) row[h * 64 + e] = acc[i][4 * h + e];
+                    if (rok && col0 + stx * 4 + h * 64 + e < n) row[h * 64 + e] = acc[i][h][e];
             } else {
                 V4 x;
-                x[0] = acc[i][4 * h];
-                x[1] = acc[i][4 * h + 1];
-                x[2] = acc[i][4 * h + 2];
-                x[3] = acc[i][4 * h + 3];
+                x[0] = acc[i][h][0];
+                x[1] = acc[i][h][1];
+                x[2] = acc[i][h][2];
+                x[3] = acc[i][h][3];
                 *reinterpret_cast<V4 *>(row + h * 64) = x;
             }
         }
@@ -1522,7 +1577,7 @@ __device__ __forceinline__ void strip_tile(T *__restrict__ d, int n, int64_t ld,
     };
     auto stash = [&](int buf) {
 #pragma unroll
-        for (int e = 0; e < EA; ++e) As[buf][ka + e][ia] = ra[e];
+        for (int e = 0; e < EA; ++e) As[buf][ka + e][ia] = first<A>(ra[e]);
 #pragma unroll
         for (int e = 0; e < EB; ++e) Bs[buf][kbr][jb + e] = rb[e];
     };
@@ -1554,7 +1609,8 @@ __device__ __forceinline__ void strip_tile(T *__restrict__ d, int n, int64_t ld,
             for (int i = 0; i < TM; ++i)
 #pragma unroll
                 for (int j = 0; j < TN; ++j)
-                    acc[i][j] = A::min3(acc[i][j], A::add(a0[i], b0[j]), A::add(a1[i], b1[j]));
+                    acc[i][j] = A::min3(acc[i][j], add_first<A>(a0[i], b0[j]),
+                                        add_first<A>(a1[i], b1[j]));
         }
         if (s + 1 < NS) stash(cur ^ 1);
         __syncthreads();
