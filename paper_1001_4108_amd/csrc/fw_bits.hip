@@ -2,9 +2,9 @@
 // blocked schedule of section 3.2 over the boolean semiring (OR for min, AND
 // for +).  Row i of the n x n matrix is ceil(n / 32) 32-bit words; bit j % 32
 // of word j / 32 is the edge (or, after the solve, the path) i -> j.  A cell
-// update of the bulk ("row i gains row k if i reaches k") is one
-// v_and_or_b32 per 32 cells: the bit of i -> k, sign-extended to a full-word
-// mask, ANDed with word w of row k and ORed into word w of row i.
+// update ("row i gains row k if i reaches k") is one v_and_or_b32 per 32 cells
+// on the vector units: the bit of i -> k, sign-extended to a full-word mask,
+// ANDed with word w of row k and ORed into word w of row i.
 //
 // k-blocks are 256 bits (8 words) wide; stage b runs
 //   bits_diag_kernel       the 256 x 256 diagonal block, closed by one wave
@@ -14,7 +14,9 @@
 //                          P <- P | D* x P (D* the closed diagonal block);
 //   bits_col_panel_kernel  columns of block b, every other 256-row block:
 //                          C <- C | C x D*;
-//   bits_bulk_kernel       the rest: X <- X | C x P.
+//   bits_bulk_mfma_kernel  the rest: X <- X | C x P, on the matrix cores;
+//   bits_bulk_kernel       the same on the vector units, where no memory can
+//                          be had for the matrix cores' operand.
 // As for distances, the panel and bulk steps are products with closed
 // blocks, so the result is exact reachability; OR is idempotent, so nothing
 // depends on the order of the updates.
@@ -157,8 +159,11 @@ constexpr int kParts = kBW / kPW;
 // Row panel: rows of block b, words w0 .. w0 + kPW - 1 of word block wb != b.
 // Thread t owns row k0 + t; the slice of every row of the block is staged in
 // S (old values) before any is written.
+// With pt non-NULL the slice also goes there transposed, the matrix bulk's
+// operand: row j of pt is column j of the row panel, 8 words of 32 k each.
 __device__ __forceinline__ void row_panel(uint32_t (*S)[kPW], uint32_t *__restrict__ bits, int n,
-                                          int64_t ldw, int nw, int b, int w0) {
+                                          int64_t ldw, int nw, int b, int w0,
+                                          uint32_t *__restrict__ pt) {
     const int t = threadIdx.x;
     const int k0 = b * kBK;
     const int i = k0 + t;
@@ -186,6 +191,23 @@ __device__ __forceinline__ void row_panel(uint32_t (*S)[kPW], uint32_t *__restri
 #pragma unroll
     for (int c = 0; c < kPW; ++c)
         if (row_ok && w0 + c < nw) bits[(int64_t)i * ldw + w0 + c] = acc[c];
+    if (pt) {
+        // the ballot of one bit over the wave's 64 rows is two words of one
+        // column; lane 32 c + s keeps that of bit s of word c
+        static_assert(kPW == 2, "64 columns, a lane each");
+        const int lane = t & 63;
+        uint32_t lo = 0, hi = 0;
+#pragma unroll
+        for (int c = 0; c < kPW; ++c)
+#pragma unroll
+            for (int s = 0; s < 32; ++s) {
+                const uint64_t m = __ballot((acc[c] >> s) & 1u);
+                lo = lane == 32 * c + s ? (uint32_t)m : lo;
+                hi = lane == 32 * c + s ? (uint32_t)(m >> 32) : hi;
+            }
+        uint2 *dst = reinterpret_cast<uint2 *>(pt + ((int64_t)w0 * 32 + lane) * kBW + 2 * (t >> 6));
+        *dst = make_uint2(lo, hi);
+    }
 }
 
 // Column panel: words w0 .. w0 + kPW - 1 (inside word block b) of the rows of
@@ -230,12 +252,13 @@ __device__ __forceinline__ void col_panel(uint32_t (*S)[kPW], uint32_t *__restri
 // row blocks, kParts workgroups per block.  The two panels write disjoint
 // words and read only their own words and the closed diagonal block.
 __global__ void __launch_bounds__(256)
-bits_panel_kernel(uint32_t *__restrict__ bits, int n, int64_t ldw, int nw, int b, int nb) {
+bits_panel_kernel(uint32_t *__restrict__ bits, int n, int64_t ldw, int nw, int b, int nb,
+                  uint32_t *__restrict__ pt) {
     __shared__ uint32_t S[kBK][kPW];
     const int x = (int)blockIdx.x / kParts, part = (int)blockIdx.x % kParts;
     if (x < nb - 1) {
         const int wb = x < b ? x : x + 1;
-        row_panel(S, bits, n, ldw, nw, b, wb * kBW + kPW * part);
+        row_panel(S, bits, n, ldw, nw, b, wb * kBW + kPW * part, pt);
     } else {
         const int y = x - (nb - 1);
         col_panel(S, bits, n, ldw, nw, b, y < b ? y : y + 1, b * kBW + kPW * part);
@@ -406,6 +429,150 @@ bits_bulk_kernel(uint32_t *__restrict__ bits, int n, int64_t ldw, int nw, int b,
     }
 }
 
+// Bulk on the matrix cores: X <- X | C x P as a product of 0/1 matrices, the
+// bits widened to 4-bit floats (0.5 per set bit) in registers.  A wave
+// computes 32 rows x 256 columns over the block's 256 k with 32 x 32 x 64
+// MFMAs; its operands are the rows' own 8 words of block b (the column panel)
+// and the 8 words of each column from pt (the row panel, transposed by the
+// panel launch), so a lane's 32 k are one word, widened by four ANDs and three
+// shifts: any order of k serves, the same on both sides.  The columns are the
+// MFMA's rows: a lane then holds 16 columns of one matrix row, and the sums,
+// started at -0.125 (0.25 per path, exact), carry the answer in their sign,
+// which one v_alignbit_b32 each shifts into the row's word.  Column 16 h + r of a
+// 32-column tile is row 8 (r / 4) + 4 h + r % 4 of the operand, so that
+// register r of half h is that bit.
+// A tile's arithmetic is short against the latency of its loads, so a
+// workgroup (four waves side by side, 1024 columns) keeps its columns' widened
+// words in registers and walks down row tiles, the next one's words and old
+// values loading while the current one is computed; the grid is what the GPU
+// holds at once.  A lane reads and writes 16 bytes of a row, two lanes 32:
+// with 64 x 128 tiles in 4-byte pieces the requests to L2 were the bound (54
+// us a launch at n=16384).
+// The waves of block b's words and the tiles of block b + 1's diagonal (closed
+// by the extra workgroup) have nothing to do.  What is computed past the matrix
+// comes from clamped rows or unwritten rows of pt (0s and 1s whatever they
+// hold) and is not stored.
+// Measured at n=16384: 33 us a launch (with the closing workgroup, which takes
+// as long) against 85 us for the vector kernel below; n=32768: 111 against 290.
+constexpr int kMR = 32, kMW = 32;  // rows and words of a workgroup's tile
+typedef int32_t v8i __attribute__((ext_vector_type(8)));
+typedef float v16f __attribute__((ext_vector_type(16)));
+typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u4u __attribute__((ext_vector_type(4), aligned(4)));
+
+// 32 bits as 32 4-bit floats, 0.5 where set (value s + 4 t in nibble t of word s)
+__device__ __forceinline__ v8i widen(uint32_t w) {
+    constexpr uint32_t m = 0x11111111u;
+    return v8i{(int)(w & m), (int)((w >> 1) & m), (int)((w >> 2) & m), (int)((w >> 3) & m),
+               0, 0, 0, 0};
+}
+
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
+bits_bulk_mfma_kernel(uint32_t *__restrict__ bits, int n, int64_t ldw, int nw, int b, int nrt,
+                      int nwt, int groups, int close_next, const uint32_t *__restrict__ pt) {
+    __shared__ __attribute__((aligned(16))) uint32_t L[kBK * kBW];
+    if (close_next && blockIdx.x == 0) {  // first, so it starts at once
+        bulk_close_next(L, bits, n, ldw, nw, b);
+        return;
+    }
+    const int wg = (int)blockIdx.x - close_next;
+    const int lane = threadIdx.x & 63, h = lane >> 5, l = lane & 31;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int k0 = b * kBK, wk0 = b * kBW, k1 = k0 + kBK, wk1 = wk0 + kBW;
+    // row tiles of block b are skipped
+    const int skip0 = k0 / kMR, nskip = min(nrt - skip0, kBK / kMR), tiles = nrt - nskip;
+    const int grp = wg / nwt, w0 = (wg - grp * nwt) * kMW + wave * 8;
+    if (w0 >= nw || w0 == wk0 || grp >= tiles) return;
+    const bool whole = w0 + 8 <= nw;  // uniform
+
+    // the columns' words 4 h .. 4 h + 3, in the operand's row order, widened
+    const int jl = 16 * ((l >> 2) & 1) + 4 * (l >> 3) + (l & 3);
+    u4 cw[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+        cw[u] = *reinterpret_cast<const u4 *>(pt + ((int64_t)(w0 + u) * 32 + jl) * kBW + 4 * h);
+
+    u4 rw, old;  // words 4 h .. 4 h + 3 of the rows' block b, and of the output
+    auto load = [&](int rt) {
+        const int i = min(rt * kMR + l, n - 1);
+        const uint32_t *row = bits + (int64_t)i * ldw;
+        const uint32_t *src = row + wk0 + 4 * h, *out = row + w0 + 4 * h;
+        if (k1 <= n) {
+            rw = *reinterpret_cast<const u4u *>(src);
+        } else {  // the last block, partial: vertices >= n dropped
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const int valid = n - (k0 + 32 * (4 * h + c));
+                const uint32_t m = valid >= 32 ? ~0u : valid <= 0 ? 0u : (1u << valid) - 1u;
+                rw[c] = valid > 0 ? src[c] & m : 0u;
+            }
+        }
+        if (whole) {
+            old = *reinterpret_cast<const u4u *>(out);
+        } else {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) old[c] = w0 + 4 * h + c < nw ? out[c] : 0u;
+        }
+    };
+    // the sums' start, kept in registers as every chain's first addend
+    v16f none;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) none[r] = -0.125f;
+    asm volatile("" : "+v"(none));
+    load(grp < skip0 ? grp : grp + nskip);
+    for (int q = grp; q < tiles; q += groups) {
+        const int row0 = (q < skip0 ? q : q + nskip) * kMR;
+        const u4 cur = rw;
+        u4 res = old;
+        const int next = q + groups;
+        if (next < tiles) load(next < skip0 ? next : next + nskip);
+        if (close_next && w0 == wk1 && row0 >= k1 && row0 < k1 + kBK) continue;
+        v8i row[4];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) row[s] = widen(cur[s]);
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            // tiles p and p + 4 (words w0 + p and w0 + 4 + p)
+            v16f x = none, y = none;
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                x = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
+                    widen(cw[p][s]), row[s], x, 4, 4, 0, 0x7f7f7f7f, 0, 0x7f7f7f7f);
+                y = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
+                    widen(cw[p + 4][s]), row[s], y, 4, 4, 0, 0x7f7f7f7f, 0, 0x7f7f7f7f);
+            }
+            uint32_t bx = 0, by = 0;  // the sign of register r in bit r
+#pragma unroll
+            for (int r = 15; r >= 0; --r) {
+                bx = __builtin_amdgcn_alignbit(bx, __float_as_uint(x[r]), 31);
+                by = __builtin_amdgcn_alignbit(by, __float_as_uint(y[r]), 31);
+            }
+            // half 0 gets both halves of tile p, half 1 those of p + 4
+            const auto z = __builtin_amdgcn_permlane32_swap(bx, by, false, false);
+            res[p] |= ~((uint32_t)z[0] | ((uint32_t)z[1] << 16));
+        }
+        const int i = row0 + l;
+        uint32_t *out = bits + (int64_t)i * ldw + w0 + 4 * h;
+        if (i < n) {
+            if (whole) {
+                *reinterpret_cast<u4u *>(out) = res;
+            } else {
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    if (w0 + 4 * h + c < nw) out[c] = res[c];
+            }
+        }
+    }
+}
+
+// Groups of row tiles per 1024-column strip: with the closing workgroup no more
+// workgroups than the GPU's 256 CUs hold at once, two each (one too many would
+// run alone after the rest).
+int mfma_groups(int nwt, int tiles) {
+    const int g = 511 / nwt;
+    return g < 1 ? 1 : g < tiles ? g : tiles;
+}
+
 // Pack / unpack between an int32 0/1 matrix and the bit layout, one wave per
 // 512 columns of a row (8 coalesced 256-byte accesses per wave); waves stride
 // over the groups, so the grid stays bounded for any n.  Pack: each lane
@@ -468,6 +635,7 @@ struct BitsStage {
     int n, nw, b, nb, nrt, nwt, close_next;
     int64_t ldw;
     hipStream_t st;
+    uint32_t *pt;  // the row panel transposed (matrix-core bulk), or NULL
 };
 
 hipError_t run_bits_diag(void *c) {
@@ -479,15 +647,24 @@ hipError_t run_bits_diag(void *c) {
 hipError_t run_bits_panels(void *c) {
     const auto *a = static_cast<const BitsStage *>(c);
     bits_panel_kernel<<<(unsigned)(2 * (a->nb - 1) * kParts), 256, 0, a->st>>>(a->bits, a->n, a->ldw,
-                                                                             a->nw, a->b, a->nb);
+                                                                             a->nw, a->b, a->nb,
+                                                                             a->pt);
     return hipGetLastError();
 }
 
 hipError_t run_bits_bulk(void *c) {
     const auto *a = static_cast<const BitsStage *>(c);
-    const int skip0 = a->b * kBK / kTR;
-    const int nskip = (a->nrt - skip0) < 4 ? (a->nrt - skip0) : 4;
+    const int rows = a->pt ? kMR : kTR;  // of a row tile
+    const int skip0 = a->b * kBK / rows;
+    const int nskip = a->nrt - skip0 < kBK / rows ? a->nrt - skip0 : kBK / rows;
     const int64_t groups = (int64_t)a->nwt * (a->nrt - nskip) + a->close_next;
+    if (a->pt) {
+        const int g = mfma_groups(a->nwt, a->nrt - nskip);
+        if (g == 0 && !a->close_next) return hipSuccess;
+        bits_bulk_mfma_kernel<<<(unsigned)((int64_t)a->nwt * g + a->close_next), 256, 0, a->st>>>(
+            a->bits, a->n, a->ldw, a->nw, a->b, a->nrt, a->nwt, g, a->close_next, a->pt);
+        return hipGetLastError();
+    }
     bits_bulk_kernel<<<(unsigned)groups, 256, 0, a->st>>>(a->bits, a->n, a->ldw, a->nw, a->b, a->nrt,
                                                          a->nwt, a->close_next);
     return hipGetLastError();
@@ -502,6 +679,7 @@ int status_of(hipError_t e) {
 int64_t words_of(int64_t n) { return (n + 31) / 32; }
 
 constexpr int64_t kMaxBitsN = 1LL << 21;
+constexpr int kMfmaMinN = kBK + 1;  // wherever there is a bulk
 
 // workgroups of the pack / unpack launches: four 512-column groups (one per
 // wave) each, at most kPackMaxBlocks (the waves then loop)
@@ -536,13 +714,32 @@ int fw_transitive_closure_bits(uint32_t *bits, int64_t n, int64_t ldw, int refle
         if (hipGetLastError() != hipSuccess) return FW_ERR_HIP;
     }
     const int nb = (nn + kBK - 1) / kBK;          // k-blocks = row blocks = word blocks
-    const int nrt = (nn + kTR - 1) / kTR;         // bulk row tiles
-    const int nwt = (nw + kTW - 1) / kTW;         // bulk word tiles
+    // The matrix-core bulk wants the row panel transposed, 32 bytes a column
+    // in stream-ordered memory of this call; without it (a stream under
+    // capture, or no memory) the vector kernel, which needs none.  The matrix
+    // cores win at every size: n=300 71 us against 98, n=1024 160 against 174,
+    // n=4096 605 against 639 (there the closing workgroup bounds both), n=16384
+    // 2.80 ms against 6.0.
+    uint32_t *pt = nullptr;
+    if (nn >= kMfmaMinN) {
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        void *mem = nullptr;
+        const size_t bytes = (size_t)((nw + kMW - 1) / kMW * kMW) * 32 * kBW * 4;
+        if (hipStreamIsCapturing(st, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone &&
+            hipMallocAsync(&mem, bytes, st) == hipSuccess)
+            pt = static_cast<uint32_t *>(mem);
+        else
+            (void)hipGetLastError();
+    }
+    const int tr = pt ? kMR : kTR, tw = pt ? kMW : kTW;
+    const int nrt = (nn + tr - 1) / tr;           // bulk row tiles
+    const int nwt = (nw + tw - 1) / tw;           // bulk word tiles
+    int status = FW_OK;
     for (int b = 0; b < nb; ++b) {
         // cell updates of each phase (for the profile counters): kb vertices
         // in block b, the rest of the matrix outside it
         const double kb = (double)(nn - b * kBK < kBK ? nn - b * kBK : kBK), rest = (double)nn - kb;
-        BitsStage a{bits, nn, nw, b, nb, nrt, nwt, b + 1 < nb ? 1 : 0, ldw, st};
+        BitsStage a{bits, nn, nw, b, nb, nrt, nwt, b + 1 < nb ? 1 : 0, ldw, st, pt};
         hipError_t e = hipSuccess;
         // later diagonal blocks are closed by the previous bulk launch
         if (b == 0) e = timed_launch(kBitsDiag, kb * kb * kb, st, run_bits_diag, &a);
@@ -553,9 +750,13 @@ int fw_transitive_closure_bits(uint32_t *bits, int64_t n, int64_t ldw, int refle
             if (e == hipSuccess)
                 e = timed_launch(kBitsBulk, rest * rest * kb + kn * kn * kn, st, run_bits_bulk, &a);
         }
-        if (e != hipSuccess) return status_of(e);
+        if (e != hipSuccess) {
+            status = status_of(e);
+            break;
+        }
     }
-    return FW_OK;
+    if (pt) (void)hipFreeAsync(pt, st);
+    return status;
 }
 
 int fw_pack_bits(const int32_t *adj, int64_t n, int64_t ld, uint32_t *bits, int64_t ldw,
