@@ -226,13 +226,20 @@ bulk_dma_kernel(T *__restrict__ d, int n, int64_t ld, int b, int m, int close_ne
     __shared__ __align__(16) T X[kCloseExtra];
     const BulkLds<T> lds = {A0, A1, B0, B1};
     if (given_up<A>(flag)) return;
+    const int last = n / S;  // blocks below it are full
+    // a partial last block's tiles take longer: from the last row upwards, so
+    // that they are not the launch's tail
+    const int dix = b * m + b, end = m * m - 1;  // dix: index of tile (b+1, b+1)
+    const bool reverse = last <= m;
     int idx = blockIdx.x;
-    const int dix = b * m + b;  // enumeration index of tile (b+1, b+1)
-    if (close_next) idx = idx == 0 ? dix : idx == dix ? 0 : idx;
+    if (close_next) {
+        const int at = reverse ? end - dix : dix;  // where its turn would be
+        idx = idx == 0 ? at : idx == at ? 0 : idx;
+    }
+    if (reverse) idx = end - idx;
     int bi, bj;
     bulk_coords(idx, b, m, bi, bj);
     const bool close = close_next && idx == dix;
-    const int last = n / S;  // blocks below it are full
     if (bi < last && bj < last && b < last && ld < (int64_t(1) << 25))
         bulk_tile_dma<T, VEC, false, A>(lds, d, n, ld, bi, bj, b, flag, acol);
     else
@@ -255,22 +262,20 @@ bulk_dma_kernel(T *__restrict__ d, int n, int64_t ld, int b, int m, int close_ne
 // panel tiles (b, j) are cut into 32-column strips, column panel tiles
 // (i, b) into 32-row strips.
 template <typename T, bool VEC, class A>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(kStripThreads)
 panel_strip_kernel(T *__restrict__ d, int n, int64_t ld, int b, int nb, int32_t *flag,
                    T *acol) {
-    constexpr int S = 128, W = 32;
-    __shared__ __align__(16) char smem[strip_smem_bytes<T, S, W, S, 16>()];  // R + CW = 160 either way
+    constexpr int S = 128, W = kStripW;
+    __shared__ __align__(16) char smem[strip_smem_bytes<T>()];
     if (given_up<A>(flag)) return;
     const int m = nb - 1;
     const int t = blockIdx.x >> 2, q = blockIdx.x & 3;
     int bi, bj;
     panel_coords(t, b, m, bi, bj);
     if (t < m)  // row panel: rows of block b, a 32-column strip of block bj
-        strip_tile<T, S, W, S, 16, 4, 4, VEC, A>(d, n, ld, b * S, bj * S + q * W, b * S, smem,
-                                                 flag);
+        strip_tile<T, S, W, VEC, A>(d, n, ld, b * S, bj * S + q * W, b * S, smem, flag);
     else        // column panel: a 32-row strip of block bi, columns of block b
-        strip_tile<T, W, S, S, 16, 4, 4, VEC, A>(d, n, ld, bi * S + q * W, b * S, b * S, smem,
-                                                 flag, acol);
+        strip_tile<T, W, S, VEC, A>(d, n, ld, bi * S + q * W, b * S, b * S, smem, flag, acol);
 }
 
 // ---------------------------------------------------------------------------
@@ -728,10 +733,10 @@ hipError_t tile_dispatch(int tile, T *d, int32_t *p, int n, int64_t ld, int64_t 
         if (mode == 0) {
             if (4 * grid > 0x7fffffffLL) return hipErrorInvalidValue;
             if (vec)
-                panel_strip_kernel<T, true, A><<<(unsigned)(4 * grid), 256, 0, st>>>(
+                panel_strip_kernel<T, true, A><<<(unsigned)(4 * grid), kStripThreads, 0, st>>>(
                     d, n, ld, b, nb, flag, acol);
             else
-                panel_strip_kernel<T, false, A><<<(unsigned)(4 * grid), 256, 0, st>>>(
+                panel_strip_kernel<T, false, A><<<(unsigned)(4 * grid), kStripThreads, 0, st>>>(
                     d, n, ld, b, nb, flag, acol);
         } else if (vec) {
             bulk_dma_kernel<T, true, A><<<(unsigned)grid, 256, 0, st>>>(d, n, ld, b, (int)m, c,

@@ -599,26 +599,37 @@ __device__ __forceinline__ void closure_blocks(T *__restrict__ d, int n, int64_t
     const int lane = threadIdx.x & 63, g = lane >> 4, cq = lane & 7;
     // a tile inside the matrix moves in 16-byte pieces (at any alignment)
     const bool full = base + S <= n;
+    // elsewhere addresses are clamped into the matrix, so that every load is
+    // issued before the first is waited for
+    auto at = [&](int r, int q) {
+        const T v = d[(int64_t)(r < n ? r : n - 1) * ld + (q < n ? q : n - 1)];
+        return r < n && q < n ? v : A::inf();
+    };
     T c[TM][TN], D[2];
-    if (!ahead) {
+    if (ahead) {
+        // the first (K, K), straight from the matrix
+#pragma unroll
+        for (int r = 0; r < 2; ++r) D[r] = at(base + 2 * g + r, base + cq);
+    } else if (full) {
 #pragma unroll
         for (int r = 0; r < TM; ++r)
 #pragma unroll
             for (int h = 0; h < TN / CW; ++h) {
                 T v[CW];
                 row_load<T, CW, false>(v, d, base + ty * TM + r, base + h * CW * G + tx * CW, n,
-                                         ld, full, A::inf());
+                                       ld, true, A::inf());
 #pragma unroll
                 for (int e = 0; e < CW; ++e) c[r][CW * h + e] = v[e];
             }
     } else {
-        // the first (K, K), straight from the matrix
 #pragma unroll
-        for (int r = 0; r < 2; ++r) {
-            T v[1];
-            row_load<T, 1, false>(v, d, base + 2 * g + r, base + cq, n, ld, full, A::inf());
-            D[r] = v[0];
-        }
+        for (int r = 0; r < TM; ++r)
+#pragma unroll
+            for (int h = 0; h < TN / CW; ++h)
+#pragma unroll
+                for (int e = 0; e < CW; ++e)
+                    c[r][CW * h + e] =
+                        at(base + ty * TM + r, base + h * CW * G + tx * CW + e);
     }
     auto put_closed = [&](T *dt) {
         close8<A>(D);
@@ -1527,128 +1538,191 @@ __device__ __forceinline__ void product_tile_key(int32_t *__restrict__ d, int32_
 }
 
 // ---------------------------------------------------------------------------
-// strip_tile: the panel update of product_tile on one strip of a panel tile,
-// R rows x CW columns with the full k-block of K, so that a stage's 2(nb-1)
-// panel tiles give four times as many workgroups (one 128 x 128 tile per
-// workgroup leaves a CU with a single wave per SIMD).  A row-panel tile is
-// cut into column strips and a column-panel tile into row strips: the panel
-// operand a strip reads (its own columns of B, or its own rows of A) is then
-// exactly the part it writes, and no two workgroups touch the same cell.
-// Same per-cell candidates as product_tile, hence the same bits.
+// strip_tile: the panel update of product_tile on one strip of a 128-wide
+// panel tile, R rows x CW columns (128 x 32 or 32 x 128) with the full k-block,
+// so that a stage's 2(nb-1) panel tiles give four times as many workgroups
+// (one 128 x 128 tile per workgroup leaves a CU with a single wave per SIMD).  A
+// row-panel tile is cut into column strips and a column-panel tile into row
+// strips: the panel operand a strip reads (its own columns of B, or its own
+// rows of A) is then exactly the part it writes, and no two workgroups touch
+// the same cell.
+// A few hundred workgroups leave this launch bound by latency, so it goes as
+// product_tile_whole: the whole k-block staged at once (80 KB, two workgroups
+// per CU), 512 threads, each half taking 64 of the k for 4 x 4 cells a thread,
+// LDS reads one step ahead.  Same per-cell candidates as product_tile, hence
+// the same bits.  Measured, fp32: 14.8 us a launch at n=6001 and 21.8 at n=16384
+// (16-deep slices in 256 threads: 19.3 and 27.1).
 // ---------------------------------------------------------------------------
-template <typename T, int R, int CW, int K, int BK>
+constexpr int kStripK = 128, kStripW = 32, kStripThreads = 512;
+template <typename T>
 constexpr int strip_smem_bytes() {
-    return 2 * BK * (R + CW) * (int)sizeof(T);
+    return kStripK * (kStripK + kStripW) * (int)sizeof(T);
 }
 
 // With the keyed policy and `acol` non-NULL (a column-panel strip of a 128-
 // wide sweep), the strip also writes its cells with the hop field cleared to
 // acol (row r, column c - col0 at acol[r * CW + c - col0]): the bulk's A
 // operand, ready to be added.
-template <typename T, int R, int CW, int K, int BK, int TM, int TN, bool VEC, class A = Ar<T>>
+template <typename T, int R, int CW, bool VEC, class A = Ar<T>>
 __device__ __forceinline__ void strip_tile(T *__restrict__ d, int n, int64_t ld, int row0,
                                            int col0, int k0, char *smem,
                                            int32_t *flag = nullptr, T *acol = nullptr) {
-    constexpr int GX = CW / TN, GY = R / TM, NT = GX * GY;
-    constexpr int EA = R * BK / NT, TPA = BK / EA;   // A slice: elements per thread
-    constexpr int EB = BK * CW / NT, TPB = CW / EB;  // B slice
-    constexpr int NS = K / BK;
-    static_assert(EA * NT == R * BK && EB * NT == BK * CW, "slice split");
-    static_assert(TPA * EA == BK && TPB * EB == CW, "slice rows");
-    static_assert(!VEC || TN % 4 == 0, "vector split");
-    // a slice share of fewer than 4 values per thread is loaded element-wise
-    constexpr bool VA = VEC && EA % 4 == 0, VB = VEC && EB % 4 == 0;
-    static_assert(BK % 2 == 0 && K % BK == 0, "k-steps are fused in pairs");
-
-    T(*As)[BK][R] = reinterpret_cast<T(*)[BK][R]>(smem);
-    T(*Bs)[BK][CW] = reinterpret_cast<T(*)[BK][CW]>(smem + 2 * BK * R * sizeof(T));
-
-    const int tid = threadIdx.x;
-    const int tx = tid % GX, ty = tid / GX;
+    constexpr int K = kStripK, TM = 4, GX = CW / 4, NT = kStripThreads;
+    constexpr int PA = R * (K / 4) / NT, PB = K * GX / NT;  // 16-byte pieces a thread stages
+    static_assert((R / TM) * GX * 2 == NT && PA >= 1 && PB >= 1, "geometry");
+    typedef typename Vec4<T>::type V4;
+    using V4g = std::conditional_t<VEC, V4, typename Vec4u<T>::type>;  // in the matrix
+    T *As = reinterpret_cast<T *>(smem), *Bs = As + R * K;
+    const int tid = threadIdx.x, half = __builtin_amdgcn_readfirstlane(tid >> 8);
+    const int cell = tid & 255, tx = cell % GX, ty = cell / GX;
     const bool full = (row0 + R <= n) && (col0 + CW <= n) && (k0 + K <= n);
-    const T INF = A::inf();
-    const int ia = tid / TPA, ka = (tid % TPA) * EA;
-    const int kbr = tid / TPB, jb = (tid % TPB) * EB;
-
-    T ra[EA], rb[EB];
-    auto fetch = [&](int s) {
-        row_load<T, EA, VA>(ra, d, row0 + ia, k0 + s * BK + ka, n, ld, full, INF);
-        row_load<T, EB, VB>(rb, d, k0 + s * BK + kbr, col0 + jb, n, ld, full, INF);
+    auto at = [&](int64_t r, int64_t c) {
+        const T v = d[(r < n ? r : n - 1) * ld + (c < n ? c : n - 1)];
+        return r < n && c < n ? v : A::inf();
     };
-    auto stash = [&](int buf) {
+    // piece p of A: k 4 (p % 32) .. of row p / 32, stored at piece ^ (row / 4);
+    // of B: columns 4 (p % GX) .. of k-row p / GX
+    V4 ra[PA], rb[PB], acc[TM];
+    if (full) {
 #pragma unroll
-        for (int e = 0; e < EA; ++e) As[buf][ka + e][ia] = first<A>(ra[e]);
+        for (int i = 0; i < PA; ++i) {
+            const int p = tid + i * NT;
+            ra[i] = *reinterpret_cast<const V4g *>(d + (int64_t)(row0 + p / (K / 4)) * ld + k0 +
+                                                   p % (K / 4) * 4);
+        }
 #pragma unroll
-        for (int e = 0; e < EB; ++e) Bs[buf][kbr][jb + e] = rb[e];
-    };
-
-    T acc[TM][TN];
+        for (int i = 0; i < PB; ++i) {
+            const int p = tid + i * NT;
+            rb[i] = *reinterpret_cast<const V4g *>(d + (int64_t)(k0 + p / GX) * ld + col0 +
+                                                   p % GX * 4);
+        }
+        if (half == 0) {
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
-        row_load<T, TN, VEC>(acc[i], d, row0 + ty * TM + i, col0 + tx * TN, n, ld, full, INF);
-    fetch(0);
-    stash(0);
-    __syncthreads();
-    for (int s = 0; s < NS; ++s) {
-        const int cur = s & 1;
-        if (s + 1 < NS) fetch(s + 1);
-#pragma unroll 1
-        for (int kk = 0; kk < BK; kk += 2) {
-            T a0[TM], a1[TM], b0[TN], b1[TN];
+            for (int i = 0; i < TM; ++i)
+                acc[i] = *reinterpret_cast<const V4g *>(d + (int64_t)(row0 + ty * TM + i) * ld +
+                                                        col0 + tx * 4);
+        }
+    } else {
+        // clamped addresses: every load is issued before the first is used
 #pragma unroll
-            for (int i = 0; i < TM; ++i) {
-                a0[i] = As[cur][kk][ty * TM + i];
-                a1[i] = As[cur][kk + 1][ty * TM + i];
+        for (int i = 0; i < PA; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int p = tid + i * NT;
+                ra[i][e] = at(row0 + p / (K / 4), k0 + p % (K / 4) * 4 + e);
             }
 #pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                b0[j] = Bs[cur][kk][tx * TN + j];
-                b1[j] = Bs[cur][kk + 1][tx * TN + j];
+        for (int i = 0; i < PB; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int p = tid + i * NT;
+                rb[i][e] = at(k0 + p / GX, col0 + p % GX * 4 + e);
             }
+        if (half == 0) {
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
-                for (int j = 0; j < TN; ++j)
-                    acc[i][j] = A::min3(acc[i][j], add_first<A>(a0[i], b0[j]),
-                                        add_first<A>(a1[i], b1[j]));
+                for (int e = 0; e < 4; ++e) acc[i][e] = at(row0 + ty * TM + i, col0 + tx * 4 + e);
         }
-        if (s + 1 < NS) stash(cur ^ 1);
-        __syncthreads();
+    }
+    if (half != 0) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[i][e] = A::top();
+    }
+#pragma unroll
+    for (int i = 0; i < PA; ++i) {
+        const int p = tid + i * NT, r = p / (K / 4), q = p % (K / 4);
+        V4 x;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[e] = first<A, T>(ra[i][e]);
+        *reinterpret_cast<V4 *>(As + r * K + (q ^ ((r >> 2) & 31)) * 4) = x;
+    }
+#pragma unroll
+    for (int i = 0; i < PB; ++i) *reinterpret_cast<V4 *>(Bs + (tid + i * NT) * 4) = rb[i];
+    __syncthreads();
+    {
+        constexpr int STEPS = K / 2 / 4;
+        const int s0 = half * STEPS;
+        V4 a[2][TM], bb[2][4];
+        auto read = [&](int s, V4(&x)[TM], V4(&y)[4]) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+                x[i] = *reinterpret_cast<const V4 *>(As + (ty * TM + i) * K + (s ^ ty) * 4);
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                y[e] = *reinterpret_cast<const V4 *>(Bs + (4 * s + e) * CW + tx * 4);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        auto apply = [&](V4(&x)[TM], V4(&y)[4]) {
+#pragma unroll
+            for (int e = 0; e < 4; e += 2) {
+                const T b0[4] = {y[e][0], y[e][1], y[e][2], y[e][3]};
+                const T b1[4] = {y[e + 1][0], y[e + 1][1], y[e + 1][2], y[e + 1][3]};
+#pragma unroll
+                for (int i = 0; i < TM; ++i) {
+                    T c[4] = {acc[i][0], acc[i][1], acc[i][2], acc[i][3]};
+                    update4<A>(c, (T)x[i][e], (T)x[i][e + 1], b0, b1);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) acc[i][j] = c[j];
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        read(s0, a[0], bb[0]);
+#pragma unroll 1
+        for (int t = 0; t < STEPS; t += 2) {
+            read(s0 + t + 1, a[1], bb[1]);
+            apply(a[0], bb[0]);
+            // (the last step reads the half's first operands again)
+            read(t + 2 < STEPS ? s0 + t + 2 : s0, a[0], bb[0]);
+            apply(a[1], bb[1]);
+        }
+    }
+    __syncthreads();
+    V4 *part = reinterpret_cast<V4 *>(smem);
+    if (half == 1) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i) part[i * 256 + cell] = acc[i];
+    }
+    __syncthreads();
+    if (half == 1) return;
+    T c[TM][4];
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+        const V4 x = part[i * 256 + cell];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) c[i][j] = A::min2(acc[i][j], x[j]);
     }
     if constexpr (A::kChecked) {
         KeyCheck bad;
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
-            for (int j = 0; j < TN; ++j) acc[i][j] = settle<A>(acc[i][j], bad);
+            for (int j = 0; j < 4; ++j) c[i][j] = settle<A>(c[i][j], bad);
         raise_flag<A>(flag, bad);
         if (acol) {
-            static_assert(TN % 4 == 0, "16-byte pieces");
 #pragma unroll
             for (int i = 0; i < TM; ++i) {
                 const int r = row0 + ty * TM + i;
-                T *dst = acol + (int64_t)r * CW + tx * TN;
+                T *dst = acol + (int64_t)r * CW + tx * 4;
                 if (full) {
+                    V4 x;
 #pragma unroll
-                    for (int j = 0; j < TN; j += 4) {
-                        typename Vec4<T>::type x;
-                        x[0] = A::clear_hop(acc[i][j]);
-                        x[1] = A::clear_hop(acc[i][j + 1]);
-                        x[2] = A::clear_hop(acc[i][j + 2]);
-                        x[3] = A::clear_hop(acc[i][j + 3]);
-                        *reinterpret_cast<typename Vec4<T>::type *>(dst + j) = x;
-                    }
+                    for (int j = 0; j < 4; ++j) x[j] = A::clear_hop(c[i][j]);
+                    *reinterpret_cast<V4 *>(dst) = x;
                 } else if (r < n) {
 #pragma unroll
-                    for (int j = 0; j < TN; ++j)
-                        if (col0 + tx * TN + j < n) dst[j] = A::clear_hop(acc[i][j]);
+                    for (int j = 0; j < 4; ++j)
+                        if (col0 + tx * 4 + j < n) dst[j] = A::clear_hop(c[i][j]);
                 }
             }
         }
     }
 #pragma unroll
     for (int i = 0; i < TM; ++i)
-        row_store<T, TN, VEC>(acc[i], d, row0 + ty * TM + i, col0 + tx * TN, n, ld, full);
+        row_store<T, 4, VEC>(c[i], d, row0 + ty * TM + i, col0 + tx * 4, n, ld, full);
 }
 
 // Tile coordinates of the stage-b panel tile number idx (0 <= idx < 2m,
