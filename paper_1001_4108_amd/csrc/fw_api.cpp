@@ -43,11 +43,12 @@ void default_plan_locked() {
         t.push_back({0, 32, 32});
         t.push_back({33, 64, 64});
         t.push_back({65, 128, 128});
-        // blocked (measured with fw_apsp_plan / fw_autotune on one MI355X):
-        // below ~4.6k (fp32) / ~4.1k (int32) vertices a stage's 128-wide bulk
-        // fills the GPU too few times and the 128-step diagonal closure
-        // weighs more, and tile 64 solves faster (n=1024: 1.7x, n=4096:
-        // 1.15x); above, tile 128's lower traffic per update wins (n=12288:
+        // blocked (measured with fw_apsp_plan on one MI355X, ms, tile 64 /
+        // 128): a stage's 128-wide bulk fills the GPU too few times below, and
+        // tile 128's lower traffic per update wins above.  fp32 n=3000 1.66 /
+        // 2.40, 4352 2.99 / 3.35, 4608 3.48 / 3.47, 5376 5.29 / 5.05, 6144 7.51 /
+        // 6.98; int32 n=3000 1.90 / 2.74, 4352 3.93 / 4.31, 4608 4.57 / 4.57, 5000
+        // 6.29 / 6.10, 6144 10.0 / 9.1 (n=12288:
         // 1.4x).  With the (distance, last hop) pair forms tile 128 never won
         // (int32 with 64-bit keys at n=8192: 69 vs 82 ms at tile 64), and
         // tile 32 wins below ~2k (fp32) / ~1k (int32) vertices (fp32 n~1448:
@@ -69,7 +70,7 @@ void default_plan_locked() {
                 t.push_back({hi32 + 1, INT64_MAX, 64});
             }
         } else {
-            const int64_t hi64 = (key & 1) == FW_F32 ? 4608 : 4096;
+            const int64_t hi64 = 4608;
             t.push_back({129, hi64, 64});
             t.push_back({hi64 + 1, INT64_MAX, 128});
         }
