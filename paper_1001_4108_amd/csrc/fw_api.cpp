@@ -240,9 +240,11 @@ int enqueue_solve(void *d, int dtype, int n, int64_t ld, int32_t *pred, int64_t 
 
 // The last hops of the fp32 canonical path (fw_internal.h), strip by strip
 // from the final distances in d and the weights saved in P, every launch
-// gated on `gate`.
+// gated on scratch[3].
 int enqueue_canon_hops(const float *d, int n, int64_t ld, int32_t *pred, int64_t ldp,
-                       float *strip, const int32_t *gate, hipStream_t st, bool capturing) {
+                       float *strip, int32_t *scratch, hipStream_t st, bool capturing) {
+    const int32_t *gate = scratch + 3;
+    int32_t *frac = scratch + 4;
     auto run = [&](auto &&launch) -> hipError_t {
         if (capturing) return launch();
         return timed(kPredFallback, 0.0, st, launch);
@@ -251,10 +253,11 @@ int enqueue_canon_hops(const float *d, int n, int64_t ld, int32_t *pred, int64_t
     const int w = canon_strip_cols(n);
     for (int j0 = 0; j0 < n && e == hipSuccess; j0 += w) {
         const int wc = std::min(w, n - j0);
-        e = run([&] { return launch_canon_strip(pred, n, ldp, j0, wc, strip, gate, st); });
+        e = run([&] { return launch_canon_strip(pred, n, ldp, j0, wc, strip, frac, gate,
+                                               st); });
         if (e == hipSuccess)
             e = run([&] {
-                return launch_canon_pred(d, n, ld, strip, j0, wc, pred, ldp, gate, st);
+                return launch_canon_pred(d, n, ld, strip, j0, wc, pred, ldp, frac, gate, st);
             });
     }
     return status_of(e);
@@ -276,8 +279,8 @@ int enqueue_canon(float *d, int n, int64_t ld, int32_t *pred, int64_t ldp, hipSt
     int s = enqueue_solve(d, FW_F32, n, ld, nullptr, 0, 64, st, capturing, kMinPlus, nullptr, gate);
     if (s != FW_OK) return s;
     return enqueue_canon_hops(d, n, ld, pred, ldp,
-                              reinterpret_cast<float *>(scratch + key_scratch_words(n)), gate, st,
-                              capturing);
+                              reinterpret_cast<float *>(scratch + key_scratch_words(n)), scratch,
+                              st, capturing);
 }
 
 // fp32 with predecessors on graphs beyond the keys' vertices: the canonical
@@ -318,7 +321,7 @@ int enqueue_canon_direct(float *d, int n, int64_t ld, int32_t *pred, int64_t ldp
     }
     if (s == FW_OK)
         s = enqueue_canon_hops(d, n, ld, pred, ldp, reinterpret_cast<float *>(scratch + 64),
-                               scratch + 3, st, capturing);
+                               scratch, st, capturing);
     if (s == FW_OK) {
         e = run(kPredFallback, [&] {
             return launch_canon_restore(d, pred, n, ld, ldp, scratch + 2, st);

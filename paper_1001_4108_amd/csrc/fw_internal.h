@@ -36,22 +36,30 @@ constexpr int kKeyMaxN = kKeyHop;
 // distances (n each); from the 64-word (256-byte) boundary after them, the
 // current stage's column panel with the hop fields cleared (n rows of 128),
 // the A operand of the 128-wide keyed bulk.  fp32 solves add, after that,
-// one strip of the original weights (n rows of canon_strip_cols(n)) for the
-// canonical path.
+// one strip of the original weights (canon_strip_cols(n) columns of it, each
+// a row of canon_ldt(n)) for the canonical path.
 constexpr int64_t key_acol_offset(int64_t n) { return (4 + 2 * n + 63) / 64 * 64; }
 constexpr int64_t key_scratch_words(int64_t n) { return key_acol_offset(n) + 128 * n; }
-constexpr int kCanonStripMax = 1024;
+// A strip's columns (stored as rows): about 2^24 weights, so that its launch
+// has some 4000 64 x 64 tiles (16 a compute unit), but no fewer than 1024 of
+// them; whole tiles.  Each is padded to whole slices of 32 vertices.
+constexpr int kCanonStripMin = 1024, kCanonSlice = 32;
+constexpr int canon_ldt(int64_t n) {
+    return (int)((n + kCanonSlice - 1) / kCanonSlice * kCanonSlice);
+}
 constexpr int canon_strip_cols(int64_t n) {
-    return (int)((n + 63) / 64 * 64 < kCanonStripMax ? (n + 63) / 64 * 64 : kCanonStripMax);
+    const int64_t all = (n + 63) / 64 * 64, want = (int64_t(1) << 24) / n / 64 * 64;
+    const int64_t cols = want < kCanonStripMin ? kCanonStripMin : want;
+    return (int)(all < cols ? all : cols);
 }
 // dtype: 0 fp32, 1 int32
 constexpr int64_t key_scratch_words_for(int dtype, int64_t n) {
-    return key_scratch_words(n) + (dtype == 0 ? n * canon_strip_cols(n) : 0);
+    return key_scratch_words(n) + (dtype == 0 ? (int64_t)canon_ldt(n) * canon_strip_cols(n) : 0);
 }
 // Scratch of an fp32 canonical path with no keyed sweep before it (graphs
 // beyond the keys' vertices): the four flag words as above (64 words), then
 // the strip.
-constexpr int64_t canon_scratch_words(int64_t n) { return 64 + n * canon_strip_cols(n); }
+constexpr int64_t canon_scratch_words(int64_t n) { return 64 + (int64_t)canon_ldt(n) * canon_strip_cols(n); }
 
 enum PhaseKind {
     kDiag = 0,
@@ -120,9 +128,11 @@ hipError_t launch_key_finish(int dtype, void *d, int32_t *keys, int n, int64_t l
 // original weights.  The predecessor matrix holds the weights meanwhile.
 //   canon_gate:  scratch[3] = (direct || scratch[0]) && !scratch[2] (the gate
 //                of the rest; direct: no keyed sweep before, scratch[2] the
-//                negative-diagonal count of the distances).
+//                negative-diagonal count of the distances); scratch[4] = 0.
 //   canon_save:  P = the bits of d (the weights); gated, counts one fallback.
-//   canon_strip: strip = columns [j0, j0 + w) of those weights (n x w, ld w).
+//   canon_strip: strip = columns [j0, j0 + w) of those weights, transposed
+//                (rows of canon_ldt(n)); *frac (scratch[4]) raised to the
+//                most bits a weight has behind the binary point.
 //   canon_pred:  columns [j0, j0 + w) of P from the final d and the strip.
 //   canon_restore: d = the weights saved in P (before the compare form that
 //                a negative diagonal takes instead).
@@ -133,9 +143,10 @@ hipError_t launch_canon_restore(float *d, const int32_t *p, int n, int64_t ld, i
 hipError_t launch_canon_save(const float *d, int32_t *p, int n, int64_t ld, int64_t ldp,
                              const int32_t *gate, hipStream_t st);
 hipError_t launch_canon_strip(const int32_t *p, int n, int64_t ldp, int j0, int w, float *strip,
-                              const int32_t *gate, hipStream_t st);
+                              int32_t *frac, const int32_t *gate, hipStream_t st);
 hipError_t launch_canon_pred(const float *d, int n, int64_t ld, const float *strip, int j0, int w,
-                             int32_t *p, int64_t ldp, const int32_t *gate, hipStream_t st);
+                             int32_t *p, int64_t ldp, const int32_t *frac, const int32_t *gate,
+                             hipStream_t st);
 // Number of gated predecessor fallbacks (64-bit or compare-form sweeps, and
 // fp32 canonical paths) that ran on the current device (synchronises the
 // device).

@@ -314,8 +314,14 @@ pred_fix_kernel(const T *__restrict__ d, int32_t *__restrict__ P, int n, int64_t
 // The fp32 canonical path (fw_internal.h): the canonical last hops from the
 // final distances and the original weights, as the oracle defines them.
 // ---------------------------------------------------------------------------
+// flag[4] is the canonical path's own word from here on (the row minima of a
+// keyed sweep end with its key_finish, which comes before): see
+// canon_strip_kernel.
 __global__ void canon_gate_kernel(int32_t *__restrict__ flag, int direct) {
-    if (threadIdx.x == 0) flag[3] = ((direct || flag[0] != 0) && flag[2] == 0) ? 1 : 0;
+    if (threadIdx.x == 0) {
+        flag[3] = ((direct || flag[0] != 0) && flag[2] == 0) ? 1 : 0;
+        flag[4] = 0;
+    }
 }
 
 // A gated save (behind a keyed sweep) counts one fallback.
@@ -339,90 +345,232 @@ canon_restore_kernel(float *__restrict__ d, const int32_t *__restrict__ P, int n
             d[(int64_t)i * ld + j] = __int_as_float(P[(int64_t)i * ldp + j]);
 }
 
+// The strip of weights, transposed: strip[c][q] = w[q][j0 + c], q padded to
+// whole slices, so that the last hops' kernel reads both of its operands
+// along q.  +INF at (j, j) (q = j is no last hop of j) and in the padding,
+// whose sums match no finite distance.  *frac becomes the largest number of
+// bits any weight has behind the binary point.
+constexpr int kCanonTile = 64, kCanonDepth = 32, kCanonGroup = 8, kCanonThreads = 256;
+static_assert(kCanonDepth == kCanonSlice, "the strip's rows are padded to whole slices");
+
+__device__ __forceinline__ int fraction_bits(float v) {
+    const uint32_t u = __float_as_uint(v), e = u >> 23 & 255;
+    if ((u << 1) == 0 || (u << 1) == 0xff000000u) return 0;  // 0, infinite
+    const uint32_t m = e ? (u & 0x7fffff) | 0x800000 : u & 0x7fffff;
+    return max(0, 150 - (int)max(e, 1u) - (__ffs((int)m) - 1));
+}
+
 __global__ void __launch_bounds__(256)
 canon_strip_kernel(const int32_t *__restrict__ P, int n, int64_t ldp, int j0, int w,
-                   float *__restrict__ strip, const int32_t *gate) {
+                   float *__restrict__ strip, int32_t *__restrict__ frac, const int32_t *gate) {
     if (gated_off(gate)) return;
-    for (int q = blockIdx.y; q < n; q += gridDim.y)
-        for (int c = blockIdx.x * 256 + threadIdx.x; c < w; c += gridDim.x * 256)
-            strip[(int64_t)q * w + c] = __int_as_float(P[(int64_t)q * ldp + j0 + c]);
+    __shared__ float t[64][65];
+    const int ldt = canon_ldt(n), tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
+    const int c0 = blockIdx.x * 64;
+    int bits = 0;
+    for (int q0 = blockIdx.y * 64; q0 < ldt; q0 += gridDim.y * 64) {
+        __syncthreads();  // the previous block's reads are done
+        for (int q = ty; q < 64; q += 4) {
+            float v = __builtin_inff();
+            if (q0 + q < n && c0 + tx < w) v = __int_as_float(P[(int64_t)(q0 + q) * ldp + j0 + c0 + tx]);
+            bits = max(bits, fraction_bits(v));
+            t[q][tx] = q0 + q == j0 + c0 + tx ? __builtin_inff() : v;
+        }
+        __syncthreads();
+        for (int c = ty; c < 64; c += 4)
+            if (q0 + tx < ldt) strip[(int64_t)(c0 + c) * ldt + q0 + tx] = t[tx][c];
+    }
+    for (int o = 32; o; o >>= 1) bits = max(bits, __shfl_xor(bits, o));
+    if (tx == 0 && bits > *frac) atomicMax(frac, bits);
 }
 
 // One 64 x 64 tile of P (rows i0.., strip columns c0..; global column j0 +
-// c) per workgroup, 4 x 4 cells per thread.  The candidates q run downward in
-// 32-deep slices staged in LDS, and a cell keeps the last q whose sum equals
-// its distance: the smallest.  A cell whose pair has no last hop (i == j,
-// or d_ij = +INF) compares against NaN, which equals nothing.  The slice of
-// d is staged with 0 at (i, i) (a path from i starts with the empty path)
-// and the strip with +INF at (j, j) (q = j is no last hop of j); rows and
-// columns beyond the matrix stage +INF, whose sums match no finite
-// distance.  No order of the sums matters: each is one fp32 add, compared
-// exactly.
-constexpr int kCanonTile = 64, kCanonDepth = 32;
+// c) per workgroup, 4 x 4 cells per thread.  A cell wants the smallest q
+// whose sum equals its distance.  The scan only finds the group of 8
+// candidates that q lies in: groups go downward, and a cell keeps the last
+// one that hit.  The cell's one group is then searched for q itself, from
+// memory.  Two forms of the hit:
+// - kMin: the smallest sum of the group is at most the distance: one add and
+//   half a minimum3 per candidate.  Where sums are exact none is below the
+//   distance, and the hit holds a match.  Where they round, one may be below
+//   it by an ulp and hide that the group has no match; the search then finds
+//   none, and the tile is scanned again in the other form.
+// - equality: some sum of the group equals the distance (an add and a
+//   compare per candidate; the lane masks are joined on the scalar unit).
+// What bounds it: instruction issue.  One candidate at a time with its own
+// compare and select (three instructions, two at the minimum's half rate, in
+// strips of 1024 columns: 3 tiles a compute unit at n=3000) took 2.93 ms at
+// n=3000 and 40.5 ms at n=8192; kMin takes 1.33 and 21.4 ms, equality 2.6 and
+// 41 (its compare still issues once per candidate).  Groups of 16 compare less
+// but search more scattered memory: 5 ms more at n=8192.  8 x 4 cells a thread
+// (180 registers, 2 waves a SIMD): 15 ms more.
+// A tile begins with kMin when its distances lie below 2^(24 - *frac) in
+// magnitude (*frac from canon_strip_kernel): sums of the weights are then
+// exact where they could reach the distance.  Either form is right for any
+// weights; beginning with kMin and going on to equality would cost both.
+// A cell whose pair has no last hop (i == j, or d_ij = +INF) compares against
+// NaN, which is neither equal to nor above anything.  The slice of d is
+// staged with 0 at (i, i) (a path from i starts with the empty path).  Rows
+// and columns beyond the matrix hold whatever the clamped row or the strip's
+// padding does: their cells compare against NaN.  No order of the sums
+// matters: each is one fp32 add, compared exactly.  fminf leaves out a NaN
+// sum (of infinite weights), which equals nothing.
+__device__ __forceinline__ uint64_t lanes_eq(float a, float b) {
+    return __builtin_amdgcn_fcmpf(a, b, 1);  // ordered, equal
+}
 
-// 8 waves per SIMD (at most 64 registers): a 1024-column strip of an
-// 8192-vertex graph (16 x 128 workgroups) is then one round of the GPU's
-// 2048 workgroup slots instead of 1.33 rounds at 6 waves.
-__global__ void __launch_bounds__(256, 8)
-canon_pred_kernel(const float *__restrict__ d, int n, int64_t ld, const float *__restrict__ strip,
-                  int j0, int w, int32_t *__restrict__ P, int64_t ldp, const int32_t *gate) {
-    if (gated_off(gate)) return;
-    constexpr int S = kCanonTile, KD = kCanonDepth;
-    __shared__ __align__(16) float As[KD][S + 4];  // As[q][r] = d[i0 + r][q0 + q]
-    __shared__ __align__(16) float Bs[KD][S + 4];  // Bs[q][c] = w[q0 + q][c0 + c]
-    const int i0 = blockIdx.y * S, c0 = blockIdx.x * S;
-    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-    const float kNaN = __builtin_nanf("");
-    float t[4][4];
-    int32_t best[4][4];
+template <bool kMin>
+__device__ __forceinline__ void canon_scan(const float *__restrict__ d, int n, int64_t ld,
+                                           const float *__restrict__ strip, int i0, int c0,
+                                           float (*As)[kCanonDepth + 4],
+                                           float (*Bs)[kCanonDepth + 4], const float (&t)[4][4],
+                                           int32_t (&grp)[4][4]) {
+    constexpr int S = kCanonTile, KD = kCanonDepth, NT = kCanonThreads, NY = 16;
+    const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
+    const int ldt = canon_ldt(n);
+    using V4u = typename Vec4u<float>::type;
+    constexpr int NL = S * KD / 4 / NT;  // 4-wide pieces of a slice per thread
+    for (int q0 = ldt - KD; q0 >= 0; q0 -= KD) {
+        float4 a[NL], b[NL];
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const int i = i0 + ty * 4 + r, cc = c0 + tx * 4 + c, j = j0 + cc;
-            float v = kNaN;
-            if (i < n && cc < w && i != j) {
-                v = d[(int64_t)i * ld + j];
-                if (v == __builtin_inff()) v = kNaN;
+        for (int l = 0; l < NL; ++l) {
+            const int e = tid + l * NT, r = e / (KD / 4), q = q0 + e % (KD / 4) * 4;
+            const int gi = min(i0 + r, n - 1);
+            const float *src = d + (int64_t)gi * ld + q;
+            if (q0 + KD <= n) {
+                const V4u x = *reinterpret_cast<const V4u *>(src);
+                a[l] = make_float4(x[0], x[1], x[2], x[3]);
+            } else {
+                a[l].x = q < n ? src[0] : __builtin_inff();
+                a[l].y = q + 1 < n ? src[1] : __builtin_inff();
+                a[l].z = q + 2 < n ? src[2] : __builtin_inff();
+                a[l].w = q + 3 < n ? src[3] : __builtin_inff();
             }
-            t[r][c] = v;
-            best[r][c] = -1;
+            a[l].x = q == gi ? 0.0f : a[l].x;
+            a[l].y = q + 1 == gi ? 0.0f : a[l].y;
+            a[l].z = q + 2 == gi ? 0.0f : a[l].z;
+            a[l].w = q + 3 == gi ? 0.0f : a[l].w;
+            b[l] = *reinterpret_cast<const float4 *>(strip + (int64_t)(c0 + r) * ldt + q);
         }
-    for (int q0 = (n - 1) / KD * KD; q0 >= 0; q0 -= KD) {
         __syncthreads();  // the previous slice's reads are done
-        for (int e = threadIdx.x; e < KD * S; e += 256) {
-            const int q = e % KD, r = e / KD, gi = i0 + r, gq = q0 + q;
-            float v = __builtin_inff();
-            if (gi < n && gq < n) v = gi == gq ? 0.0f : d[(int64_t)gi * ld + gq];
-            As[q][r] = v;
-        }
-        for (int e = threadIdx.x; e < KD * S; e += 256) {
-            const int c = e % S, q = e / S, gq = q0 + q, cc = c0 + c;
-            float v = __builtin_inff();
-            if (gq < n && cc < w && gq != j0 + cc) v = strip[(int64_t)gq * w + cc];
-            Bs[q][c] = v;
+#pragma unroll
+        for (int l = 0; l < NL; ++l) {
+            const int e = tid + l * NT, r = e / (KD / 4), q = e % (KD / 4) * 4;
+            *reinterpret_cast<float4 *>(&As[r][q]) = a[l];
+            *reinterpret_cast<float4 *>(&Bs[r][q]) = b[l];
         }
         __syncthreads();
-#pragma unroll 4
-        for (int q = KD - 1; q >= 0; --q) {
-            const float4 a = *reinterpret_cast<const float4 *>(&As[q][ty * 4]);
-            const float4 b = *reinterpret_cast<const float4 *>(&Bs[q][tx * 4]);
-            const float av[4] = {a.x, a.y, a.z, a.w}, bv[4] = {b.x, b.y, b.z, b.w};
-            const int32_t gq = q0 + q;
+#pragma unroll 1
+        for (int g = KD - kCanonGroup; g >= 0; g -= kCanonGroup) {
+            float m[4][4];
+            uint64_t eq[4][4];  // lane masks
+#pragma unroll
+            for (int k = 0; k < kCanonGroup; k += 4) {
+                float4 bv[4];
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    bv[c] = *reinterpret_cast<const float4 *>(&Bs[tx + 16 * c][g + k]);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const float4 av = *reinterpret_cast<const float4 *>(&As[ty + NY * r][g + k]);
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        const float x0 = av.x + bv[c].x, x1 = av.y + bv[c].y;
+                        const float x2 = av.z + bv[c].z, x3 = av.w + bv[c].w;
+                        if constexpr (kMin) {
+                            const float y = __builtin_fminf(x0, x1);
+                            m[r][c] = k == 0 ? y : __builtin_fminf(__builtin_fminf(m[r][c], x0), x1);
+                            m[r][c] = __builtin_fminf(__builtin_fminf(m[r][c], x2), x3);
+                        } else {
+                            const float v = t[r][c];
+                            const uint64_t h = lanes_eq(x0, v) | lanes_eq(x1, v) |
+                                               lanes_eq(x2, v) | lanes_eq(x3, v);
+                            eq[r][c] = k == 0 ? h : (eq[r][c] | h);
+                        }
+                    }
+                }
+            }
 #pragma unroll
             for (int r = 0; r < 4; ++r)
 #pragma unroll
-                for (int c = 0; c < 4; ++c)
-                    best[r][c] = av[r] + bv[c] == t[r][c] ? gq : best[r][c];
+                for (int c = 0; c < 4; ++c) {
+                    bool hit;
+                    if constexpr (kMin) hit = m[r][c] <= t[r][c];
+                    else hit = __builtin_amdgcn_inverse_ballot_w64(eq[r][c]);
+                    grp[r][c] = hit ? q0 + g : grp[r][c];
+                }
         }
     }
+}
+
+__global__ void __launch_bounds__(kCanonThreads)
+canon_pred_kernel(const float *__restrict__ d, int n, int64_t ld, const float *__restrict__ strip,
+                  int j0, int w, int32_t *__restrict__ P, int64_t ldp,
+                  const int32_t *__restrict__ frac, const int32_t *gate) {
+    if (gated_off(gate)) return;
+    constexpr int S = kCanonTile, KD = kCanonDepth, NY = 16, NT = kCanonThreads;
+    __shared__ __align__(16) float lds[2 * S * (KD + 4)];
+    float(*As)[KD + 4] = reinterpret_cast<float(*)[KD + 4]>(lds);  // As[r][q] = d[i0+r][q0+q]
+    float(*Bs)[KD + 4] = As + S;                                   // Bs[c][q] = w[q0+q][c0+c]
+    static_assert(2 * (KD + 4) >= S, "the groups take the slices' place");
+    const int i0 = blockIdx.y * S, c0 = blockIdx.x * S;
+    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
+    const int ldt = canon_ldt(n);
+    const float limit = __builtin_ldexpf(1.0f, 24 - *frac);
+    bool inexact = false;
+    float t[4][4];
+    int32_t grp[4][4];
 #pragma unroll
     for (int r = 0; r < 4; ++r)
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
-            const int i = i0 + ty * 4 + r, cc = c0 + tx * 4 + c;
-            if (i < n && cc < w) P[(int64_t)i * ldp + j0 + cc] = best[r][c];
+            const int i = i0 + ty + NY * r, cc = c0 + tx + 16 * c, j = j0 + cc;
+            float v = __builtin_nanf("");
+            if (i < n && cc < w && i != j) {
+                v = d[(int64_t)i * ld + j];
+                if (v == __builtin_inff()) v = __builtin_nanf("");
+            }
+            inexact = inexact || __builtin_fabsf(v) >= limit;
+            t[r][c] = v;
         }
+    for (bool equal = __syncthreads_or(inexact);; equal = true) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) grp[r][c] = -1;
+        if (equal)
+            canon_scan<false>(d, n, ld, strip, i0, c0, As, Bs, t, grp);
+        else
+            canon_scan<true>(d, n, ld, strip, i0, c0, As, Bs, t, grp);
+        // The groups go through LDS, so that the search is a short loop whose
+        // registers are not the scan's.
+        int32_t *G = reinterpret_cast<int32_t *>(lds);
+        __syncthreads();  // the last slice's reads are done
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) G[(ty + NY * r) * S + tx + 16 * c] = grp[r][c];
+        __syncthreads();
+        bool miss = false;
+#pragma unroll 2
+        for (int e = threadIdx.x; e < S * S; e += NT) {
+            const int i = i0 + e / S, cc = c0 + e % S, q0 = G[e];
+            int32_t best = -1;
+            if (q0 >= 0) {
+                const float v = d[(int64_t)i * ld + j0 + cc];
+                const float *ra = d + (int64_t)i * ld + q0;
+                const float *rb = strip + (int64_t)cc * ldt + q0;
+#pragma unroll
+                for (int q = kCanonGroup - 1; q >= 0; --q) {
+                    const float x = q0 + q < n ? ra[q] : __builtin_inff();
+                    best = (q0 + q == i ? 0.0f : x) + rb[q] == v ? q0 + q : best;
+                }
+                miss = miss || best < 0;
+            }
+            if (i < n && cc < w) P[(int64_t)i * ldp + j0 + cc] = best;
+        }
+        if (equal || !__syncthreads_or(miss)) break;
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -898,20 +1046,22 @@ hipError_t launch_canon_save(const float *d, int32_t *p, int n, int64_t ld, int6
 }
 
 hipError_t launch_canon_strip(const int32_t *p, int n, int64_t ldp, int j0, int w, float *strip,
-                              const int32_t *gate, hipStream_t st) {
+                              int32_t *frac, const int32_t *gate, hipStream_t st) {
     if (n <= 0 || w <= 0 || j0 < 0 || j0 + w > n) return hipErrorInvalidValue;
-    const int gx = (w + 255) / 256, gy = n < 8192 / gx ? n : 8192 / gx;
+    const int gx = (w + 63) / 64, gy = std::min((canon_ldt(n) + 63) / 64, std::max(1, 8192 / gx));
     canon_strip_kernel<<<dim3((unsigned)gx, (unsigned)gy), 256, 0, st>>>(p, n, ldp, j0, w, strip,
-                                                                         gate);
+                                                                         frac, gate);
     return hipGetLastError();
 }
 
 hipError_t launch_canon_pred(const float *d, int n, int64_t ld, const float *strip, int j0, int w,
-                             int32_t *p, int64_t ldp, const int32_t *gate, hipStream_t st) {
+                             int32_t *p, int64_t ldp, const int32_t *frac, const int32_t *gate,
+                             hipStream_t st) {
     if (n <= 0 || w <= 0 || j0 < 0 || j0 + w > n) return hipErrorInvalidValue;
     const dim3 g((unsigned)((w + kCanonTile - 1) / kCanonTile),
                  (unsigned)((n + kCanonTile - 1) / kCanonTile));
-    canon_pred_kernel<<<g, 256, 0, st>>>(d, n, ld, strip, j0, w, p, ldp, gate);
+    canon_pred_kernel<<<g, kCanonThreads, 0, st>>>(d, n, ld, strip, j0, w, p, ldp, frac,
+                                                   gate);
     return hipGetLastError();
 }
 
