@@ -48,8 +48,8 @@ void default_plan_locked() {
         // tile 128's lower traffic per update wins above.  fp32 n=3000 1.66 /
         // 2.40, 4352 2.99 / 3.35, 4608 3.48 / 3.47, 5376 5.29 / 5.05, 6144 7.51 /
         // 6.98; int32 n=3000 1.90 / 2.74, 4352 3.93 / 4.31, 4608 4.57 / 4.57, 5000
-        // 6.29 / 6.10, 6144 10.0 / 9.1 (n=12288:
-        // 1.4x).  With the (distance, last hop) pair forms tile 128 never won
+        // 6.29 / 6.10, 6144 10.0 / 9.1; at n=12288 fp32 tile 128 is 1.4x faster.
+        // With the (distance, last hop) pair forms tile 128 never won
         // (int32 with 64-bit keys at n=8192: 69 vs 82 ms at tile 64), and
         // tile 32 wins below ~2k (fp32) / ~1k (int32) vertices (fp32 n~1448:
         // 4.0 vs 4.6 ms; int32 n~724: 0.78 vs 0.83).  These entries pick the
@@ -265,7 +265,7 @@ int enqueue_canon_hops(const float *d, int n, int64_t ld, int32_t *pred, int64_t
 
 // The fp32 canonical path behind a keyed sweep, every launch gated on
 // scratch[3]: the weights saved in P, the distances by the distances-only
-// sweep at tile 64 (the register-staged tiles take a gate), then P.
+// sweep at tile 64 (whose kernels take a gate), then P.
 int enqueue_canon(float *d, int n, int64_t ld, int32_t *pred, int64_t ldp, hipStream_t st,
                   bool capturing, int32_t *scratch) {
     const int32_t *gate = scratch + 3;

@@ -7,12 +7,14 @@
 //
 //   1. diag_kernel   -- the "independent block" (b, b): s dependent k-steps
 //                       on one tile.
-//   2. tile_kernel   -- the "singly dependent" row panel (b, j != b) and
-//      (mode 0)         column panel (i != b, b).
-//   3. tile_kernel   -- the "doubly dependent" bulk (i != b, j != b), the
-//      (mode 1)         phase that sets the speed of the whole algorithm.
+//   2. panels        -- the "singly dependent" row panel (b, j != b) and
+//                       column panel (i != b, b).
+//   3. bulk          -- the "doubly dependent" tiles (i != b, j != b), the
+//                       phase that sets the speed of the whole algorithm.
 //
-// Phases 2 and 3 share one kernel because both are the same tile update
+// The panels and the bulk run tile64_kernel at tile 64 (modes of one kernel),
+// panel_strip_kernel and bulk_dma_kernel at tile 128, and tile_kernel at tile
+// 32 and with predecessors.  Both phases are the same tile update
 //     C(i,j) <- min(C(i,j), min_{k in block b} A(i,k) + B(k,j))
 // with A = tile (bi, b) and B = tile (b, bj) read at the moment the phase
 // starts.  For the bulk this is the paper's order-free doubly dependent
@@ -846,8 +848,8 @@ hipError_t tile_dispatch(int tile, T *d, int32_t *p, int n, int64_t ld, int64_t 
                          int nb, int mode, bool close_next, hipStream_t st, int32_t *flag,
                          const int32_t *gate) {
     // gates: the predecessor forms (the pair-form sweep behind a keyed one),
-    // and without predecessors the register-staged tiles (the distances of
-    // the fp32 canonical path)
+    // and without predecessors tiles 64 and 32 (the distances of the fp32
+    // canonical path)
     if (gate && !p && tile > 64) return hipErrorInvalidValue;
     const int64_t m = nb - 1;
     const int64_t grid = mode == 0 ? 2 * m : m * m;

@@ -12,8 +12,9 @@
 //   rung 2  64 x 64 tiles, 4 x 4 cells per thread in registers with two
 //           k-steps fused into a three-input minimum, the whole A and B tiles
 //           in LDS (64 KB per workgroup);
-//   rung 3  the same with the operands staged through LDS in 16-deep k-slices
-//           (16 KB per workgroup): the library's tile-64 path;
+//   rung 3  the library's tile-64 path: the operands' 64-deep k-block copied to
+//           LDS at once and read ahead of its use, C in registers (32 KB per
+//           workgroup), the next diagonal closed in the bulk;
 //   rung 4  the library's 128-wide path (direct global->LDS slice copies,
 //           8 x 8 cells per thread, strip panels, the next diagonal closed in
 //           the bulk), which the plan table picks for large solves.

@@ -564,11 +564,11 @@ __device__ __forceinline__ T sum8(T x, V4 a0, V4 a1, V4 b0, V4 b1) {
 // (K', K') as its owners hold it.
 // Every geometry and both forms take the same sums, so a tile's bits do not
 // depend on them.
-// Measured (one 64-wide tile, launches back to back): 9.4 us ahead (512 + 64
-// threads), 13.2 us in 256 threads, against 12 us and, in a 256-thread bulk
-// workgroup, 13 us for two plain steps per barrier; 16-vertex sub-blocks
-// took 9.8 us (the closing wave's share grows with the square of their width).
-// 128-wide: 31 us ahead against 37 us.
+// Measured (one tile, launches back to back; in brackets two plain steps per
+// barrier): 64-wide 8.1 us ahead (512 + 64 threads) and 12.4 us in 256 threads
+// (14.7), 32-wide 3.7 us (5.2), 128-wide 29.1 us ahead (38.3).  16-vertex
+// sub-blocks were slower (the closing wave's share grows with the square of
+// their width): n=512 158 us the solve against 150.
 constexpr int kCloseLd = kClosureK + 4;  // 16-byte pieces of D's columns in different banks
 static_assert(kCloseExtra == 2 * kClosureK * kCloseLd + 2 * kClosureK * kClosureK, "dt, t");
 template <typename T>
@@ -1006,8 +1006,8 @@ __device__ __forceinline__ void product_tile(T *__restrict__ d, int32_t *__restr
 // of row r at p ^ (r / 4) (the 4 rows a wave reads at once fall in different
 // banks), B as in memory.  Same candidates as product_tile, hence the same
 // bits.  Measured (with the closure above): n=512 fp32 252 -> 144 us, n=1500
-// 804 -> 608 us, and, at one half per tile and five workgroups per CU, n=4096
-// 3.26 -> 2.65 ms: the read-ahead loop also beats product_tile's where the
+// 806 -> 607 us, and, at one half per tile and five workgroups per CU, n=4096
+// 3.25 -> 2.62 ms: the read-ahead loop also beats product_tile's where the
 // launch fills the GPU.
 // ---------------------------------------------------------------------------
 template <typename T>
