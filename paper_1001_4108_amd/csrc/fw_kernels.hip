@@ -353,6 +353,7 @@ canon_restore_kernel(float *__restrict__ d, const int32_t *__restrict__ P, int n
 // whose sums match no finite distance.  *frac becomes the largest number of
 // bits any weight has behind the binary point.
 constexpr int kCanonTile = 64, kCanonDepth = 32, kCanonGroup = 8, kCanonThreads = 256;
+constexpr int32_t kCanonAgain = -3;  // no last hop: the tile is left to the equality launch
 static_assert(kCanonDepth == kCanonSlice, "the strip's rows are padded to whole slices");
 
 __device__ __forceinline__ int fraction_bits(float v) {
@@ -396,17 +397,20 @@ canon_strip_kernel(const int32_t *__restrict__ P, int n, int64_t ldp, int j0, in
 //   half a minimum3 per candidate.  Where sums are exact none is below the
 //   distance, and the hit holds a match.  Where they round, one may be below
 //   it by an ulp and hide that the group has no match; the search then finds
-//   none, and the tile is scanned again in the other form.
+//   none, and the tile is left to the other form.
 // - equality: some sum of the group equals the distance (an add and a
 //   compare per candidate; the lane masks are joined on the scalar unit).
 // What bounds it: instruction issue.  One candidate at a time with its own
 // compare and select (three instructions, two at the minimum's half rate, in
 // strips of 1024 columns: 3 tiles a compute unit at n=3000) took 2.93 ms at
-// n=3000 and 40.5 ms at n=8192; kMin takes 1.33 and 21.4 ms, equality 2.6 and
-// 41 (its compare still issues once per candidate).  Groups of 16 compare less
+// n=3000 and 40.5 ms at n=8192; kMin takes 1.33 and 21.4 ms, equality 2.0 and
+// 36 (its compare still issues once per candidate).  Groups of 16 compare less
 // but search more scattered memory: 5 ms more at n=8192.  8 x 4 cells a thread
 // (180 registers, 2 waves a SIMD): 15 ms more.
-// A tile begins with kMin when its distances lie below 2^(24 - *frac) in
+// Two launches, so that each form has its own registers: the first scans the
+// tiles it may by kMin (102 registers) and marks the others in P, the second
+// scans those by equality at six waves a SIMD (both forms in one kernel of four:
+// reals 63.5 ms the solve at n=8192 against 58.1, at n=16400 486 against 445).  A tile begins with kMin when its distances lie below 2^(24 - *frac) in
 // magnitude (*frac from canon_strip_kernel): sums of the weights are then
 // exact where they could reach the distance.  Either form is right for any
 // weights; beginning with kMin and going on to equality would cost both.
@@ -505,7 +509,8 @@ __device__ __forceinline__ void canon_scan(const float *__restrict__ d, int n, i
     }
 }
 
-__global__ void __launch_bounds__(kCanonThreads)
+template <bool kMin>
+__global__ void __launch_bounds__(kCanonThreads, kMin ? 4 : 6)
 canon_pred_kernel(const float *__restrict__ d, int n, int64_t ld, const float *__restrict__ strip,
                   int j0, int w, int32_t *__restrict__ P, int64_t ldp,
                   const int32_t *__restrict__ frac, const int32_t *gate) {
@@ -518,6 +523,9 @@ canon_pred_kernel(const float *__restrict__ d, int n, int64_t ld, const float *_
     const int i0 = blockIdx.y * S, c0 = blockIdx.x * S;
     const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
     const int ldt = canon_ldt(n);
+    int32_t *const mark = P + (int64_t)i0 * ldp + j0 + c0;
+    if constexpr (!kMin)
+        if (*mark != kCanonAgain) return;
     const float limit = __builtin_ldexpf(1.0f, 24 - *frac);
     bool inexact = false;
     float t[4][4];
@@ -535,44 +543,46 @@ canon_pred_kernel(const float *__restrict__ d, int n, int64_t ld, const float *_
             inexact = inexact || __builtin_fabsf(v) >= limit;
             t[r][c] = v;
         }
-    for (bool equal = __syncthreads_or(inexact);; equal = true) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-#pragma unroll
-            for (int c = 0; c < 4; ++c) grp[r][c] = -1;
-        if (equal)
-            canon_scan<false>(d, n, ld, strip, i0, c0, As, Bs, t, grp);
-        else
-            canon_scan<true>(d, n, ld, strip, i0, c0, As, Bs, t, grp);
-        // The groups go through LDS, so that the search is a short loop whose
-        // registers are not the scan's.
-        int32_t *G = reinterpret_cast<int32_t *>(lds);
-        __syncthreads();  // the last slice's reads are done
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-#pragma unroll
-            for (int c = 0; c < 4; ++c) G[(ty + NY * r) * S + tx + 16 * c] = grp[r][c];
-        __syncthreads();
-        bool miss = false;
-#pragma unroll 2
-        for (int e = threadIdx.x; e < S * S; e += NT) {
-            const int i = i0 + e / S, cc = c0 + e % S, q0 = G[e];
-            int32_t best = -1;
-            if (q0 >= 0) {
-                const float v = d[(int64_t)i * ld + j0 + cc];
-                const float *ra = d + (int64_t)i * ld + q0;
-                const float *rb = strip + (int64_t)cc * ldt + q0;
-#pragma unroll
-                for (int q = kCanonGroup - 1; q >= 0; --q) {
-                    const float x = q0 + q < n ? ra[q] : __builtin_inff();
-                    best = (q0 + q == i ? 0.0f : x) + rb[q] == v ? q0 + q : best;
-                }
-                miss = miss || best < 0;
-            }
-            if (i < n && cc < w) P[(int64_t)i * ldp + j0 + cc] = best;
+    if constexpr (kMin)
+        if (__syncthreads_or(inexact)) {
+            if (threadIdx.x == 0) *mark = kCanonAgain;
+            return;
         }
-        if (equal || !__syncthreads_or(miss)) break;
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) grp[r][c] = -1;
+    canon_scan<kMin>(d, n, ld, strip, i0, c0, As, Bs, t, grp);
+    // The groups go through LDS, so that the search is a short loop whose
+    // registers are not the scan's.
+    int32_t *G = reinterpret_cast<int32_t *>(lds);
+    __syncthreads();  // the last slice's reads are done
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) G[(ty + NY * r) * S + tx + 16 * c] = grp[r][c];
+    __syncthreads();
+    bool miss = false;
+#pragma unroll 2
+    for (int e = threadIdx.x; e < S * S; e += NT) {
+        const int i = i0 + e / S, cc = c0 + e % S, q0 = G[e];
+        int32_t best = -1;
+        if (q0 >= 0) {
+            const float v = d[(int64_t)i * ld + j0 + cc];
+            const float *ra = d + (int64_t)i * ld + q0;
+            const float *rb = strip + (int64_t)cc * ldt + q0;
+#pragma unroll
+            for (int q = kCanonGroup - 1; q >= 0; --q) {
+                const float x = q0 + q < n ? ra[q] : __builtin_inff();
+                best = (q0 + q == i ? 0.0f : x) + rb[q] == v ? q0 + q : best;
+            }
+            miss = miss || best < 0;
+        }
+        if (i < n && cc < w) P[(int64_t)i * ldp + j0 + cc] = best;
     }
+    // (thread 0 wrote that cell itself)
+    if constexpr (kMin)
+        if (__syncthreads_or(miss) && threadIdx.x == 0) *mark = kCanonAgain;
 }
 
 // ---------------------------------------------------------------------------
@@ -1062,8 +1072,10 @@ hipError_t launch_canon_pred(const float *d, int n, int64_t ld, const float *str
     if (n <= 0 || w <= 0 || j0 < 0 || j0 + w > n) return hipErrorInvalidValue;
     const dim3 g((unsigned)((w + kCanonTile - 1) / kCanonTile),
                  (unsigned)((n + kCanonTile - 1) / kCanonTile));
-    canon_pred_kernel<<<g, kCanonThreads, 0, st>>>(d, n, ld, strip, j0, w, p, ldp, frac,
-                                                   gate);
+    canon_pred_kernel<true><<<g, kCanonThreads, 0, st>>>(d, n, ld, strip, j0, w, p, ldp, frac,
+                                                         gate);
+    canon_pred_kernel<false><<<g, kCanonThreads, 0, st>>>(d, n, ld, strip, j0, w, p, ldp, frac,
+                                                          gate);
     return hipGetLastError();
 }
 
