@@ -43,11 +43,10 @@ PROFILE = os.path.join(ROOT, "profiles", "bulk_dma_kernel_f32_t128_n16384.md")
 KERNEL_SOURCES = ("paper_1001_4108_amd/csrc/fw_tiles.h", "paper_1001_4108_amd/csrc/fw_kernels.hip")
 BITS_PROFILE = os.path.join(ROOT, "profiles", "bits_kernels_reachability_n16384.md")
 BITS_SOURCES = ("paper_1001_4108_amd/csrc/fw_bits.hip",)
-# Bit-packed reachability: the bulk needs 1.125 lane-instructions per 32-cell
-# word-update (one v_and_or_b32, plus one v_bfe_i32 per 8 words); its peak is
-# the published lane-operation rate at that count
-BITS_INSTR_PER_WORD = 1.125
-BITS_WORD_PEAK = VALU_LANE_OPS_PER_S / BITS_INSTR_PER_WORD
+# Bit-packed reachability: the bulk is a 0/1 product on the matrix cores in
+# fp4, two operations per cell of a 32-cell word-update; its peak is the
+# published dense fp4 rate (10 PFLOP/s) at that count
+BITS_WORD_PEAK = 10e15 / 64
 
 
 def measured_traffic(profile=PROFILE, sources=KERNEL_SOURCES):
@@ -377,7 +376,7 @@ def bench_closure(torch, fw, gen, dev, n=16384, reps=5):
     words_per_launch = float(n - kb) * (nw - (kb + 31) // 32) * kb  # every stage: one block out
     avg_us = bulk_ms * 1e3 / max(bulk_launches, 1)
     achieved = words_per_launch / (avg_us * 1e-6) if avg_us > 0 else 0.0
-    roofline = {"bound": "alu", "kernel": "bits_bulk_kernel (bulk tiles + next diagonal block)",
+    roofline = {"bound": "alu", "kernel": "bits_bulk_mfma_kernel (bulk tiles + next diagonal block)",
                 "achieved": achieved / 1e12, "peak": BITS_WORD_PEAK / 1e12,
                 "unit": "T word-updates/s (32 cells each)", "frac": achieved / BITS_WORD_PEAK,
                 "traffic": measured_traffic(BITS_PROFILE, BITS_SOURCES),
