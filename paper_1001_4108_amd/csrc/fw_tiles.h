@@ -311,7 +311,8 @@ __device__ __forceinline__ T add_first(T a, T b) {
 // clock per CU of a possible 107; with two registers of its own per cell and a
 // one-cycle gap before each minimum it issues 69 (n=8192 int32: 24.4 -> 19.9
 // ms, with predecessors 25.6 -> 21.1; without the gap 22.7, with the eight adds
-// first 21.6, with a gap of three cycles 22.5).  fp32 is fastest as the compiler
+// first 21.6, with a gap of three cycles 22.5).  A minimum is written before later
+// cells read their operands, hence the early clobbers.  fp32 is fastest as the compiler
 // orders it (n=16384 110 ms against 116-139 in these forms).
 template <class A, typename T>
 __device__ __forceinline__ void update4(T (&c)[4], T a0, T a1, const T *b0, const T *b1) {
@@ -323,9 +324,9 @@ __device__ __forceinline__ void update4(T (&c)[4], T a0, T a1, const T *b0, cons
     "s_nop 0\n\t"                                                                    \
     "v_min3_i32 %[c" #i "], %[c" #i "], %[s" #i "], %[t" #i "]\n\t"
         asm(FW_CELL(0) FW_CELL(1) FW_CELL(2) FW_CELL(3)
-            : [c0] "+v"(c[0]), [c1] "+v"(c[1]), [c2] "+v"(c[2]), [c3] "+v"(c[3]), [s0] "=&v"(s[0]),
-              [s1] "=&v"(s[1]), [s2] "=&v"(s[2]), [s3] "=&v"(s[3]), [t0] "=&v"(t[0]),
-              [t1] "=&v"(t[1]), [t2] "=&v"(t[2]), [t3] "=&v"(t[3])
+            : [c0] "+&v"(c[0]), [c1] "+&v"(c[1]), [c2] "+&v"(c[2]), [c3] "+&v"(c[3]),
+              [s0] "=&v"(s[0]), [s1] "=&v"(s[1]), [s2] "=&v"(s[2]), [s3] "=&v"(s[3]),
+              [t0] "=&v"(t[0]), [t1] "=&v"(t[1]), [t2] "=&v"(t[2]), [t3] "=&v"(t[3])
             : [a] "v"(a0), [b] "v"(a1), [p0] "v"(b0[0]), [p1] "v"(b0[1]), [p2] "v"(b0[2]),
               [p3] "v"(b0[3]), [q0] "v"(b1[0]), [q1] "v"(b1[1]), [q2] "v"(b1[2]), [q3] "v"(b1[3]));
 #undef FW_CELL
