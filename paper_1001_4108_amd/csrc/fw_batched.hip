@@ -305,24 +305,50 @@ constexpr bool staged_can_close() {
     return staged_tm<T, S, PRED>() == staged_tn<T, S, PRED>() && (S <= 64 || PRED);
 }
 
-// Diagonal tiles of stage b of many graphs, in the geometry of the
+// Diagonal tiles of stage b of many graphs, in the geometries of the
 // single-graph phase-1 kernel (a plan with predecessors may hold graphs
 // without: both forms then share the predecessor form's geometry).
-template <typename T, int S, bool PRED>
-__global__ void __launch_bounds__((closure_threads<T, S, PRED, Ar<T>, false>()))
+template <typename T, int S, bool PRED, bool AHEAD>
+__global__ void __launch_bounds__((closure_threads<T, S, PRED, Ar<T>, AHEAD>()))
 staged_diag_kernel(const BatchItem *items, const StagedWork *work, int b) {
-    constexpr int kSmem = closure_smem_bytes<T, S, PRED>() > closure_smem_bytes<T, S, false>()
-                              ? closure_smem_bytes<T, S, PRED>()
-                              : closure_smem_bytes<T, S, false>();
-    constexpr int TM = closure_tm<T, S, PRED, Ar<T>, false>();
-    constexpr int TN = closure_tn<T, S, PRED, Ar<T>, false>();
+    constexpr int kSmem =
+        closure_smem_bytes<T, S, PRED>() > closure_smem_bytes<T, S, false, AHEAD>()
+            ? closure_smem_bytes<T, S, PRED>()
+            : closure_smem_bytes<T, S, false, AHEAD>();
+    constexpr int TM = closure_tm<T, S, PRED, Ar<T>, AHEAD>();
+    constexpr int TN = closure_tn<T, S, PRED, Ar<T>, AHEAD>();
     __shared__ __align__(16) char smem[kSmem];
     const BatchItem it = items[work[blockIdx.x].item];
     T *d = as_global(static_cast<T *>(it.d));
     if (PRED && it.p != nullptr)
         closure_tile<T, S, TM, PRED>(d, as_global(it.p), it.n, it.ld, it.ldp, b * S, smem);
     else
-        closure_tile_any<T, S, TM, false, Ar<T>, TN>(d, nullptr, it.n, it.ld, 0, b * S, smem);
+        closure_tile_any<T, S, TM, false, Ar<T>, TN, AHEAD>(d, nullptr, it.n, it.ld, 0, b * S,
+                                                            smem);
+}
+
+// 128-wide launches of at most one tile per CU take the form that closes ahead:
+// each tile then has a CU to itself, and the form with the shorter chain ends
+// sooner (64 to 256 fp32 graphs of 128 vertices as one captured launch: 36-38
+// us, in 256 threads 54-56, in 1024 threads with two plain steps a barrier
+// 45-48).  With more tiles the 256-thread form, of which several share a CU
+// (512 graphs: 62 us, ahead 68; 4096: 309, ahead 492).  At 64 and 32 the two
+// forms take the same time up to 512 graphs, and the smaller one less beyond.
+#ifndef FW_STAGED_AHEAD_MAX
+#define FW_STAGED_AHEAD_MAX 256
+#endif
+template <typename T, int S, bool PRED>
+void launch_staged_diag(const BatchItem *items, const StagedWork *work, int b, unsigned grid,
+                        hipStream_t st) {
+    if constexpr (!PRED && S == 128) {
+        if (grid <= FW_STAGED_AHEAD_MAX) {
+            staged_diag_kernel<T, S, false, true>
+                <<<grid, closure_threads<T, S, false, Ar<T>, true>(), 0, st>>>(items, work, b);
+            return;
+        }
+    }
+    staged_diag_kernel<T, S, PRED, false>
+        <<<grid, closure_threads<T, S, PRED, Ar<T>, false>(), 0, st>>>(items, work, b);
 }
 
 // ---------------------------------------------------------------------------
@@ -536,9 +562,9 @@ hipError_t launch_staged_t(int tile, const BatchItem *items, const StagedWork *w
     }
     if (kind == kStagedDiag) {
         switch (tile) {
-        case 32: staged_diag_kernel<T, 32, PRED><<<grid, closure_threads<T, 32, PRED, Ar<T>, false>(), 0, st>>>(items, work, b); break;
-        case 64: staged_diag_kernel<T, 64, PRED><<<grid, closure_threads<T, 64, PRED, Ar<T>, false>(), 0, st>>>(items, work, b); break;
-        case 128: staged_diag_kernel<T, 128, PRED><<<grid, closure_threads<T, 128, PRED, Ar<T>, false>(), 0, st>>>(items, work, b); break;
+        case 32: launch_staged_diag<T, 32, PRED>(items, work, b, grid, st); break;
+        case 64: launch_staged_diag<T, 64, PRED>(items, work, b, grid, st); break;
+        case 128: launch_staged_diag<T, 128, PRED>(items, work, b, grid, st); break;
         default: return hipErrorInvalidValue;
         }
         return hipGetLastError();
@@ -842,8 +868,8 @@ int build_host_plan(void *const *d, const int64_t *n, const int64_t *ld, int64_t
         // the bulk launch of stage b closes each graph's tile (b+1, b+1)
         // tile 128 without predecessors: panels and bulk run staged_tile_dma
         // (rows 16-byte aligned in every graph of the group); each stage
-        // keeps its diagonal launch, whose 1024-thread workgroups close a
-        // tile sooner than a 256-thread bulk workgroup would after its product
+        // keeps its diagonal launch: a closure after its product would hold
+        // the bulk launch back
         bool dma = tile == 128 && !any_pred && FW_STAGED_DMA;
         for (int32_t g : gs) {
             const BatchItem &it = items[(size_t)g];

@@ -590,6 +590,7 @@ __device__ __forceinline__ void closure_blocks(T *__restrict__ d, int n, int64_t
     static_assert(G % 16 == 0 && TN % CW == 0 && K % TM == 0 && WR % 8 == 0, "geometry");
     typedef typename Vec4<T>::type V4;
     typedef T VW __attribute__((ext_vector_type(CW)));
+    typedef T VP __attribute__((ext_vector_type(CW), aligned(4)));  // in the matrix
     typedef T VQ __attribute__((ext_vector_type(QS)));
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const bool ahead = AHEAD && wave == NW / 64;  // the wave that closes ahead
@@ -622,15 +623,32 @@ __device__ __forceinline__ void closure_blocks(T *__restrict__ d, int n, int64_t
 #pragma unroll
                 for (int e = 0; e < CW; ++e) c[r][CW * h + e] = v[e];
             }
+    } else if (n >= CW) {
+        // whole pieces here too: one that reaches past the last column starts
+        // earlier, and its values move up (element by element a 100-vertex
+        // tile took 256 threads 4 us more)
+#pragma unroll
+        for (int r = 0; r < TM; ++r)
+#pragma unroll
+            for (int h = 0; h < TN / CW; ++h) {
+                const int gi = base + ty * TM + r, gj = base + h * CW * G + tx * CW;
+                const int from = gj < n - CW ? gj : n - CW;
+                const T *src = d + (int64_t)(gi < n ? gi : n - 1) * ld + from;
+                const VP x = *reinterpret_cast<const VP *>(src);
+#pragma unroll
+                for (int e = 0; e < CW; ++e) {
+                    T v = x[e];
+#pragma unroll
+                    for (int m = e + 1; m < CW; ++m) v = gj - from == m - e ? (T)x[m] : v;
+                    c[r][CW * h + e] = gi < n && gj + e < n ? v : A::inf();
+                }
+            }
     } else {
 #pragma unroll
         for (int r = 0; r < TM; ++r)
 #pragma unroll
-            for (int h = 0; h < TN / CW; ++h)
-#pragma unroll
-                for (int e = 0; e < CW; ++e)
-                    c[r][CW * h + e] =
-                        at(base + ty * TM + r, base + h * CW * G + tx * CW + e);
+            for (int j = 0; j < TN; ++j)
+                c[r][j] = at(base + ty * TM + r, base + j / CW * CW * G + tx * CW + j % CW);
     }
     auto put_closed = [&](T *dt) {
         close8<A>(D);
@@ -790,8 +808,8 @@ __device__ __forceinline__ void closure_blocks(T *__restrict__ d, int n, int64_t
                 T v[CW];
 #pragma unroll
                 for (int e = 0; e < CW; ++e) v[e] = c[r][CW * h + e];
-                row_store<T, CW, false>(v, d, base + sty * TM + r, base + h * CW * G + stx * CW,
-                                          n, ld, full);
+                const int gi = base + sty * TM + r, gj = base + h * CW * G + stx * CW;
+                row_store<T, CW, false>(v, d, gi, gj, n, ld, full || (gi < n && gj + CW <= n));
             }
     }
     if (ahead) __builtin_amdgcn_s_setprio(0);

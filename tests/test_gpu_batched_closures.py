@@ -1,0 +1,83 @@
+"""The 128-wide diagonal launches of a batch: at most one tile per CU (256) and
+more take closures of different geometries, with the same sums as a solve alone;
+tiles of part of the matrix move in whole pieces.  Counts on both sides of the
+line, the edges of pieces of two and four columns, the smallest matrices, rows of
+any alignment; and a launch with a CU per tile takes no longer than one tile."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_1001_4108_amd as fw
+from paper_1001_4108_amd import gen
+
+pytestmark = pytest.mark.gpu
+
+
+def _padded(w, pad, fill):
+    n = w.shape[0]
+    host = np.full((n, n + pad), fill, dtype=w.dtype)
+    host[:, :n] = w
+    t = torch.from_numpy(host).cuda()
+    return t[:, :n], t
+
+
+@pytest.mark.parametrize("count", [256, 257])
+@pytest.mark.parametrize("n,pad", [(66, 0), (97, 1), (126, 2), (127, 0), (128, 3), (200, 0)])
+def test_bits_of_a_solve_alone(n, pad, count):
+    """Fractional fp32 weights, whose sums round."""
+    rng = np.random.default_rng((n, count))
+    w = gen.dense_graph(n, 0.4, 1, 50, seed=(n, pad)) + rng.random((n, n), dtype=np.float32)
+    np.fill_diagonal(w, 0)
+    alone = torch.from_numpy(w).cuda()
+    batch = [_padded(w, pad, np.float32(7)) for _ in range(count)]
+    try:
+        fw.plan_set("f32", n, n, 128)
+        fw.fw_apsp_plan(alone, 128)
+        fw.fw_apsp_batched([v for v, _ in batch])
+    finally:
+        fw.plan_reset()
+    for v, whole in batch:
+        assert torch.equal(v.contiguous().view(torch.int32), alone.view(torch.int32))
+        assert (whole[:, n:] == 7).all()
+
+
+@pytest.mark.parametrize("tile", [32, 64, 128])
+@pytest.mark.parametrize("pad", [0, 1])
+@pytest.mark.parametrize("dtype", [np.float32, np.int32])
+@pytest.mark.parametrize("n", [2, 3, 4, 5, 6, 7, 29, 30, 61, 63, 125, 126])
+def test_part_of_a_tile(n, pad, dtype, tile):
+    w = gen.dense_graph(n, 0.5, 1, 100, seed=(n, pad), dtype=dtype)
+    v, whole = _padded(w, pad, dtype(7))
+    fw.fw_apsp_plan(v, tile)
+    assert np.array_equal(v.cpu().numpy(), oracle.fw(w))
+    assert (whole[:, n:] == 7).all()
+
+
+def _replay_us(plan, reps=50, groups=7):
+    times = []
+    for _ in range(groups + 1):  # the first a warm-up
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        for _ in range(reps):
+            plan.launch("graph")
+        b.record()
+        b.synchronize()
+        times.append(a.elapsed_time(b) * 1e3 / reps)
+    return min(times[1:])
+
+
+def test_a_cu_per_tile_takes_as_long_as_one_tile():
+    """64 graphs of 128 vertices against one: a quarter of the GPU's 256 CUs each
+    close one tile.  The 256-thread closure, made to share a CU, takes 1.5
+    times as long; 1.3 lies between."""
+    one = torch.zeros((128, 128), device="cuda")
+    many = torch.zeros((64, 128, 128), device="cuda")
+    solve, batch = fw.SolvePlan(one), fw.BatchPlan([many[g] for g in range(64)])
+    try:
+        alone, together = _replay_us(solve), _replay_us(batch)
+    finally:
+        solve.destroy()
+        batch.destroy()
+    print(f"[batched closures] one {alone:.1f} us, 64 {together:.1f} us", flush=True)
+    assert together <= 1.3 * alone
