@@ -81,3 +81,34 @@ def test_a_cu_per_tile_takes_as_long_as_one_tile():
         batch.destroy()
     print(f"[batched closures] one {alone:.1f} us, 64 {together:.1f} us", flush=True)
     assert together <= 1.3 * alone
+
+
+@pytest.mark.parametrize("extra", ["one", "below", "grid", "above", "twice"])
+def test_persistent_counts(extra):
+    """Graphs of the persistent kernel: fewer than its workgroups (each takes
+    the graph of its own number), as many, and more (the rest from the counter),
+    on every launch of a plan."""
+    many = [torch.zeros((2, 2), device="cuda") for _ in range(8192)]
+    plan = fw.BatchPlan(many)
+    grid = plan.grid
+    plan.destroy()
+    assert 1 < grid < 8192
+    count = {"one": 1, "below": grid - 1, "grid": grid, "above": grid + 1,
+             "twice": 2 * grid + 3}[extra]
+    rng = np.random.default_rng(count)
+    sizes = rng.integers(1, 9, count)
+    sizes[0] = 8
+    graphs = [gen.dense_graph(int(n), 0.5, 1, 50, seed=(g, int(n))) for g, n in enumerate(sizes)]
+    want = [oracle.fw(w) for w in graphs]
+    src = [torch.from_numpy(w).cuda() for w in graphs]
+    d = [s.clone() for s in src]
+    plan = fw.BatchPlan(d)
+    try:
+        for mode in ("kernel", "graph", "graph"):
+            for a, b in zip(d, src):
+                a.copy_(b)
+            plan.launch(mode)
+            torch.cuda.synchronize()
+            assert all(np.array_equal(a.cpu().numpy(), w) for a, w in zip(d, want)), mode
+    finally:
+        plan.destroy()
