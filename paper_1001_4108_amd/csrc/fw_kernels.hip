@@ -585,6 +585,38 @@ canon_pred_kernel(const float *__restrict__ d, int n, int64_t ld, const float *_
         if (__syncthreads_or(miss) && threadIdx.x == 0) *mark = kCanonAgain;
 }
 
+// The same for small matrices: a wave for 64 cells of one row, each lane through
+// every candidate of its column, one launch for any weights.  64 x 64 cells a
+// workgroup leave most CUs idle here, and the groups and the second launch cost
+// more than they save: a captured solve of reals n=64 79 -> 48 us, n=128 122 ->
+// 77, n=512 414 -> 332; of halves n=512 361 -> 333, but n=700 528 -> 594, where
+// the L2 has to feed every candidate of every cell.  Hence the line at 512.
+constexpr int kCanonSmallMax = 512;
+__global__ void __launch_bounds__(64)
+canon_pred_small_kernel(const float *__restrict__ d, int n, int64_t ld,
+                        const float *__restrict__ strip, int j0, int w, int32_t *__restrict__ P,
+                        int64_t ldp, const int32_t *gate) {
+    if (gated_off(gate)) return;
+    const int ldt = canon_ldt(n), i = blockIdx.y, c = blockIdx.x * 64 + threadIdx.x, j = j0 + c;
+    const float *row = d + (int64_t)i * ld, *col = strip + (int64_t)c * ldt;
+    float v = row[min(j, n - 1)];
+    if (i == j || v == __builtin_inff()) v = __builtin_nanf("");
+    int32_t best = -1;
+#pragma unroll 2
+    for (int q0 = ldt - 8; q0 >= 0; q0 -= 8) {
+        const float4 lo = *reinterpret_cast<const float4 *>(col + q0);
+        const float4 hi = *reinterpret_cast<const float4 *>(col + q0 + 4);
+        const float b[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+#pragma unroll
+        for (int e = 7; e >= 0; --e) {
+            const int q = q0 + e;  // past n: the strip's padding matches nothing
+            const float a = q == i ? 0.0f : row[min(q, n - 1)];
+            best = a + b[e] == v ? q : best;
+        }
+    }
+    if (j < j0 + w) P[(int64_t)i * ldp + j] = best;
+}
+
 // ---------------------------------------------------------------------------
 // The keyed int32 predecessor solve (keys as in fw_internal.h).
 // ---------------------------------------------------------------------------
@@ -1070,6 +1102,11 @@ hipError_t launch_canon_pred(const float *d, int n, int64_t ld, const float *str
                              int32_t *p, int64_t ldp, const int32_t *frac, const int32_t *gate,
                              hipStream_t st) {
     if (n <= 0 || w <= 0 || j0 < 0 || j0 + w > n) return hipErrorInvalidValue;
+    if (n <= kCanonSmallMax) {
+        canon_pred_small_kernel<<<dim3((unsigned)((w + 63) / 64), (unsigned)n), 64, 0, st>>>(
+            d, n, ld, strip, j0, w, p, ldp, gate);
+        return hipGetLastError();
+    }
     const dim3 g((unsigned)((w + kCanonTile - 1) / kCanonTile),
                  (unsigned)((n + kCanonTile - 1) / kCanonTile));
     canon_pred_kernel<true><<<g, kCanonThreads, 0, st>>>(d, n, ld, strip, j0, w, p, ldp, frac,
