@@ -46,11 +46,15 @@ namespace fw {
 namespace {
 
 // 64-wide launches of at most this many tiles take two halves of k per tile
-// (512 threads): up to about two such workgroups per CU a launch lasts as
-// long as one of them (n=512 144 us against 178, n=1500, 529 bulk tiles, 608
-// against 650), beyond that the joining of the halves costs more than it
-// saves (n=2000, 961 tiles, 961 us against 857).
-constexpr int64_t kTile64SplitMax = 576;
+// (512 threads): the launch lasts as long as its last round of workgroups, and a
+// tile in halves ends sooner; with more tiles the joining of the halves costs
+// more than that saves.  Solves in one launch a stage of k^2 tiles, one half a
+// tile against two, n = 64 (k + 1) with aligned rows, then 37 vertices fewer with
+// unaligned ones: k=23 fp32 564 / 440 and 635 / 607 us, int32 601 / 488 and 676 /
+// 662; k=26 638 / 504 and 720 / 704, 680 / 563 and 765 / 763; k=27 670 / 592 and
+// 753 / 756, 712 / 667 and 800 / 834; k=29 725 / 666 and 810 / 894, 768 / 747 and
+// 859 / 977.  The line is where the unaligned ones cross.
+constexpr int64_t kTile64SplitMax = 700;
 
 // A gated launch (gate != NULL) does nothing unless *gate != 0: the 64-bit
 // predecessor sweep queued behind a keyed one runs only when the keyed one
