@@ -1,7 +1,8 @@
 """The 128-wide diagonal launches of a batch: at most one tile per CU (256) and
 more take closures of different geometries, with the same sums as a solve alone;
 tiles of part of the matrix move in whole pieces.  Counts on both sides of the
-line, the edges of pieces of two and four columns, the smallest matrices, rows of
+line, the edges of pieces of two and four columns and of the 8-vertex sub-blocks, the
+smallest matrices, rows of
 any alignment; and a launch with a CU per tile takes no longer than one tile."""
 import numpy as np
 import pytest
@@ -45,7 +46,7 @@ def test_bits_of_a_solve_alone(n, pad, count):
 @pytest.mark.parametrize("tile", [32, 64, 128])
 @pytest.mark.parametrize("pad", [0, 1])
 @pytest.mark.parametrize("dtype", [np.float32, np.int32])
-@pytest.mark.parametrize("n", [2, 3, 4, 5, 6, 7, 29, 30, 61, 63, 125, 126])
+@pytest.mark.parametrize("n", [2, 3, 4, 5, 6, 7, 8, 9, 15, 23, 24, 25, 29, 30, 61, 63, 125, 126])
 def test_part_of_a_tile(n, pad, dtype, tile):
     w = gen.dense_graph(n, 0.5, 1, 100, seed=(n, pad), dtype=dtype)
     v, whole = _padded(w, pad, dtype(7))
