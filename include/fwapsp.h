@@ -108,9 +108,11 @@ int fw_apsp_i32(int32_t *d, int64_t n, int64_t ld, void *stream);
  * With pred and 2 <= n <= 16383 the (distance, last hop) pairs are first
  * swept as 32-bit integer keys (distance * 2^14 + last hop) held in `pred`,
  * at the cost of the int32 distances-only sweep; this takes 16 + 8n + 512n
- * bytes (rounded to 256), and for fp32 another 4 n min(n rounded up to 64,
- * 1024) bytes, of stream-ordered device memory (hipMallocAsync on `stream`,
- * freed on it).  When an entry of d is not an integer with |w| < 2^14
+ * bytes (rounded to 256), and for fp32 another 4 R C bytes (R: n rounded up to
+ * 32; C: the smaller of n rounded up to 64 and 2^24 / n rounded down to 64, but
+ * of the latter at least 1024; 36 MB at n=3000, about 64 MiB from n=4096 on), of
+ * stream-ordered device memory (hipMallocAsync on `stream`, freed on it; a solve
+ * plan holds as much).  When an entry of d is not an integer with |w| < 2^14
  * (fp32: also a fraction), some distance met during that sweep has
  * |d| >= 2^14, or a diagonal entry ends negative, a second form already
  * queued behind it (each launch gated on a device flag) solves again from
@@ -126,8 +128,8 @@ int fw_apsp_i32(int32_t *d, int64_t n, int64_t ld, void *stream);
  * directly: the weights saved in `pred`, the distances-only sweep, then
  * every last hop from the definition; after a negative diagonal instead the
  * compare form from the saved weights (counted by fw_pred_fallbacks).  This
- * takes 256 + 4 n min(n rounded up to 64, 1024) bytes of stream-ordered
- * device memory; where it cannot be had, the compare form runs alone.
+ * takes 256 + 4096 R bytes (R: n rounded up to 32) of stream-ordered device
+ * memory; where it cannot be had, the compare form runs alone.
  * Errors: as fw_apsp, plus FW_ERR_INVALID for a bad dtype or, with pred
  * non-NULL, ld_pred < n or n*ld_pred overflowing int64.
  */
@@ -176,6 +178,10 @@ int fw_apsp_semiring(void *d, int dtype, int semiring, int64_t n, int64_t ld, vo
  *   reflexive  non-zero: every vertex reaches itself (the diagonal is set
  *              first); zero: paths of one edge or more only (i reaches i iff
  *              i lies on a cycle).
+ * For n > 256 the call takes 32 bytes per column (columns rounded up to 1024) of
+ * stream-ordered device memory, freed on `stream`.  While `stream` is being
+ * captured, and where the memory cannot be had, it takes none and runs another
+ * form: the same result, in up to 2.5 times the time (n=32768; 1.1 at n=1024).
  * Stream-ordered.  Errors: FW_ERR_INVALID for bits == NULL with n > 0, n < 0
  * or ldw too small; FW_ERR_UNSUPPORTED for n > 2^21 (a 512 GiB matrix).
  */
@@ -235,8 +241,9 @@ void fw_plan_reset(void);
  *      k-ordered diagonal and panel phases;
  *   2  blocked, 64 x 64 tiles, 4 x 4 register sub-tiles, two k-steps fused,
  *      the whole operand tiles in LDS (64 KB per workgroup);
- *   3  as 2 with the operands staged in 16-deep LDS slices (the tile-64 path
- *      of fw_apsp_plan);
+ *   3  as 2 in 32 KB of LDS, with LDS reads one step ahead of their use and the
+ *      next diagonal tile closed in the bulk launch (the tile-64 path of
+ *      fw_apsp_plan);
  *   4  tile 128: direct global->LDS slice copies, 8 x 8 register sub-tiles,
  *      strip panels, the next diagonal tile closed in the bulk launch (the
  *      path the plan table picks for large solves; rung 3 is its pick for
@@ -311,7 +318,11 @@ int fw_autotune_batch(int dtype, const int64_t *n, int64_t count, const int64_t 
  *            NULL) to int32 predecessor matrices with leading dimensions
  *            ld_pred[g] (ld_pred may be NULL only if pred is NULL).
  *   count    number of graphs (0 = no-op).
- * A graph's result is bit-identical to fw_apsp_pred on the same graph alone.
+ * A graph's result is bit-identical to fw_apsp_pred on the same graph alone --
+ * except fp32 with a predecessor matrix where sums round (fractional weights,
+ * say): a batch takes the compare form there and fw_apsp_pred the canonical
+ * path, so both results are valid by the exactness rule but may differ in last
+ * bits, and in last hops that hang on them.
  * Errors: FW_ERR_INVALID if any graph's arguments are invalid (nothing is
  * enqueued), FW_ERR_UNSUPPORTED if a graph exceeds fw_batched_max_n().
  * The call uploads the descriptor table and the stage-batched work table
@@ -365,7 +376,8 @@ int64_t fw_batched_max_n(int dtype, int with_pred);
  *      later launch (one graph launch per batch);
  *   2  no persistent kernel: every graph through the single-graph stage
  *      loop of fw_apsp_pred (the per-graph launch baseline).
- * All modes give bit-identical results.  Launches of one plan must not
+ * All modes give bit-identical results (mode 2 with the exception named at
+ * fw_apsp_batched).  Launches of one plan must not
  * overlap in time (they share the work counter).  fw_batch_plan_destroy synchronises
  * the device and frees the plan.  fw_batch_plan_grid returns the persistent
  * grid size (workgroups), or -1 for a NULL plan.

@@ -39,7 +39,7 @@ void default_plan_locked() {
     for (int key = 0; key < 4; ++key) {
         std::vector<PlanEntry> &t = g_plan[key];
         t.clear();
-        // n <= tile: one closure over the whole graph (the plain algorithm)
+        // n <= tile: one closure over the whole graph
         t.push_back({0, 32, 32});
         t.push_back({33, 64, 64});
         t.push_back({65, 128, 128});

@@ -13,14 +13,16 @@
 // streams of the plan.  The smaller graphs go through one
 // persistent launch in which each workgroup repeatedly takes the next graph
 // from a device work counter (largest first) and solves it alone:
-//   * n <= tile: the diagonal closure over the whole graph -- the plain
-//     algorithm of section 3.1;
+//   * n <= tile: the diagonal closure over the whole graph (with predecessors
+//     the plain algorithm of section 3.1);
 //   * n >  tile: the blocked schedule run inside the workgroup (diagonal
 //     tile, panel tiles, bulk tiles, workgroup barriers between the phases).
 // The tile comes from the same plan table as single-graph solves, and every
 // cell takes the same candidates in the same order as there (the same code
 // from fw_tiles.h, or staged_tile_dma's same sums), so a graph's bits do not
-// depend on whether it was solved alone or in a batch.
+// depend on whether it was solved alone or in a batch -- except fp32 with
+// predecessors where sums round: a batch takes the compare form, a solve alone
+// the canonical path.
 //
 // No workgroup ever waits for another one, so every grid drains.
 #include <hip/hip_runtime.h>

@@ -452,8 +452,10 @@ bits_bulk_kernel(uint32_t *__restrict__ bits, int n, int64_t ldw, int nw, int b,
 // by the extra workgroup) have nothing to do.  What is computed past the matrix
 // comes from clamped rows or unwritten rows of pt (0s and 1s whatever they
 // hold) and is not stored.
-// Measured at n=16384: 33 us a launch (with the closing workgroup, which takes
-// as long) against 85 us for the vector kernel below; n=32768: 111 against 290.
+// Measured at n=16384: 32 us a launch (31 without the closing workgroup) against
+// 85 us for the vector kernel below; n=32768: 111 against 290.  What bounds it:
+// the matrix cores are busy 41% of a launch, the vector instructions (widening,
+// signs) issue for another 39%, and with two waves a SIMD the two hardly overlap.
 constexpr int kMR = 32, kMW = 32;  // rows and words of a workgroup's tile
 typedef int32_t v8i __attribute__((ext_vector_type(8)));
 typedef float v16f __attribute__((ext_vector_type(16)));

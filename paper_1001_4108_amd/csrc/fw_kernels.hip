@@ -412,11 +412,13 @@ canon_strip_kernel(const int32_t *__restrict__ P, int n, int64_t ldp, int j0, in
 // but search more scattered memory: 5 ms more at n=8192.  8 x 4 cells a thread
 // (180 registers, 2 waves a SIMD): 15 ms more.
 // Two launches, so that each form has its own registers: the first scans the
-// tiles it may by kMin (102 registers) and marks the others in P, the second
-// scans those by equality at six waves a SIMD (both forms in one kernel of four:
-// reals 63.5 ms the solve at n=8192 against 58.1, at n=16400 486 against 445).  A tile begins with kMin when its distances lie below 2^(24 - *frac) in
-// magnitude (*frac from canon_strip_kernel): sums of the weights are then
-// exact where they could reach the distance.  Either form is right for any
+// tiles it may by kMin (102 registers, 48 bytes of scratch a lane) and marks the
+// others in P, the second scans those by equality at six waves a SIMD (80
+// registers, 7 spilled: 64 bytes of scratch; both forms in one kernel of four:
+// reals 63.5 ms the solve at n=8192 against 58.1, at n=16400 486 against 445).  A
+// tile begins with kMin when its distances lie below 2^(24 - *frac) in magnitude
+// (*frac from canon_strip_kernel): sums of the weights are then exact where they
+// could reach the distance.  Either form is right for any
 // weights; beginning with kMin and going on to equality would cost both.
 // A cell whose pair has no last hop (i == j, or d_ij = +INF) compares against
 // NaN, which is neither equal to nor above anything.  The slice of d is
@@ -813,11 +815,14 @@ dim3 elementwise_grid(int n) {
 }
 
 // ---------------------------------------------------------------------------
-// Dispatch: compile-time tile configurations.
-//   tile  BK  TM x TN  threads   diag TM (threads)
-//   128   16   8 x 8     256       4 (1024)
-//    64   16   4 x 4     256       4 (256)
-//    32   16   4 x 4      64       2 (256)
+// Dispatch: compile-time tile configurations.  Cells per thread and threads:
+//   tile  panels and bulk                        diagonal (with predecessors, or
+//                                                 keys; closure_threads)
+//   128   strips 4 x 4 (512), bulk 8 x 8 (256)   4 x 8, 512 + 64 (4 x 4, 1024)
+//    64   4 x 4 (256, or 512 in two halves)      2 x 4, 512 + 64 (4 x 4, 256)
+//    32   4 x 4 (64)                             2 x 2, 256 + 64 (2 x 2, 256)
+// With predecessors panels and bulk are the register-staged tile_kernel: 4 x 4
+// cells, 1024, 256 and 64 threads (keyed at 128: see tile_t).
 // ---------------------------------------------------------------------------
 template <typename T, bool PRED, class A>
 hipError_t diag_t(int tile, T *d, int32_t *p, int n, int64_t ld, int64_t ldp, int b,

@@ -5,10 +5,13 @@
 // batched kernel (one graph per workgroup, fw_batched.hip), so a graph gets
 // the same per-cell candidate sequence -- hence the same bits -- either way.
 //
-//   closure_tile  -- Floyd-Warshall (section 3.1, Fig. FW-Alg) restricted to
+//   closure_tile_any -- Floyd-Warshall (section 3.1, Fig. FW-Alg) restricted to
 //                    one s x s tile whose origin is on the diagonal: the
-//                    paper's "independent block" (section 3.2).  When the
-//                    tile covers the whole graph this IS the plain algorithm.
+//                    paper's "independent block" (section 3.2).  With
+//                    predecessors (closure_tile) step by step, so that a tile
+//                    over the whole graph IS the plain algorithm; without them
+//                    (closure_blocks) in 8-vertex sub-blocks, the same results
+//                    in exact arithmetic from sums in another association.
 //   product_tile  -- C <- min(C, A (x) B) over one k-block: the paper's
 //                    "doubly dependent" update (section 3.2) with A = tile
 //                    (bi, b), B = tile (b, bj), C = tile (bi, bj).

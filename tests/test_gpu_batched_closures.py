@@ -1,9 +1,9 @@
 """The 128-wide diagonal launches of a batch: at most one tile per CU (256) and
 more take closures of different geometries, with the same sums as a solve alone;
 tiles of part of the matrix move in whole pieces.  Counts on both sides of the
-line, the edges of pieces of two and four columns and of the 8-vertex sub-blocks, the
-smallest matrices, rows of
-any alignment; and a launch with a CU per tile takes no longer than one tile."""
+line, the edges of pieces of two and four columns and of the 8-vertex sub-blocks,
+the smallest matrices, rows of any alignment; and a launch with a CU per tile
+takes no longer than one tile."""
 import numpy as np
 import pytest
 import torch
