@@ -331,21 +331,12 @@ staged_diag_kernel(const BatchItem *items, const StagedWork *work, int b) {
                                                             smem);
 }
 
-// 128-wide launches of at most one tile per CU take the form that closes ahead:
-// each tile then has a CU to itself, and the form with the shorter chain ends
-// sooner (64 to 256 fp32 graphs of 128 vertices as one captured launch: 36-38
-// us, in 256 threads 54-56, in 1024 threads with two plain steps a barrier
-// 45-48).  With more tiles the 256-thread form, of which several share a CU
-// (512 graphs: 62 us, ahead 68; 4096: 309, ahead 492).  At 64 and 32 the two
-// forms take the same time up to 512 graphs, and the smaller one less beyond.
-#ifndef FW_STAGED_AHEAD_MAX
-#define FW_STAGED_AHEAD_MAX 256
-#endif
+// `ahead`: the form that closes ahead (closes_ahead; 128-wide, no predecessors).
 template <typename T, int S, bool PRED>
 void launch_staged_diag(const BatchItem *items, const StagedWork *work, int b, unsigned grid,
-                        hipStream_t st) {
+                        bool ahead, hipStream_t st) {
     if constexpr (!PRED && S == 128) {
-        if (grid <= FW_STAGED_AHEAD_MAX) {
+        if (ahead) {
             staged_diag_kernel<T, S, false, true>
                 <<<grid, closure_threads<T, S, false, Ar<T>, true>(), 0, st>>>(items, work, b);
             return;
@@ -558,7 +549,7 @@ staged_dma_kernel(const BatchItem *__restrict__ items, const StagedWork *__restr
 
 template <typename T, bool PRED>
 hipError_t launch_staged_t(int tile, const BatchItem *items, const StagedWork *work, int kind,
-                           int b, unsigned grid, hipStream_t st) {
+                           int b, unsigned grid, bool ahead, hipStream_t st) {
     if (kind == kStagedBulkDma || kind == kStagedPanelDma) {
         if (PRED || tile != 128) return hipErrorInvalidValue;
         staged_dma_kernel<T><<<grid, 256, 0, st>>>(items, work, kind, b);
@@ -566,9 +557,9 @@ hipError_t launch_staged_t(int tile, const BatchItem *items, const StagedWork *w
     }
     if (kind == kStagedDiag) {
         switch (tile) {
-        case 32: launch_staged_diag<T, 32, PRED>(items, work, b, grid, st); break;
-        case 64: launch_staged_diag<T, 64, PRED>(items, work, b, grid, st); break;
-        case 128: launch_staged_diag<T, 128, PRED>(items, work, b, grid, st); break;
+        case 32: launch_staged_diag<T, 32, PRED>(items, work, b, grid, ahead, st); break;
+        case 64: launch_staged_diag<T, 64, PRED>(items, work, b, grid, ahead, st); break;
+        case 128: launch_staged_diag<T, 128, PRED>(items, work, b, grid, ahead, st); break;
         default: return hipErrorInvalidValue;
         }
         return hipGetLastError();
@@ -592,13 +583,14 @@ hipError_t launch_staged_t(int tile, const BatchItem *items, const StagedWork *w
 }
 
 hipError_t launch_staged(int dtype, bool pred, int tile, const BatchItem *items,
-                         const StagedWork *work, int kind, int b, unsigned grid, hipStream_t st) {
+                         const StagedWork *work, int kind, int b, unsigned grid, bool ahead,
+                         hipStream_t st) {
     if (grid == 0) return hipSuccess;
     if (dtype == FW_F32)
-        return pred ? launch_staged_t<float, true>(tile, items, work, kind, b, grid, st)
-                    : launch_staged_t<float, false>(tile, items, work, kind, b, grid, st);
-    return pred ? launch_staged_t<int32_t, true>(tile, items, work, kind, b, grid, st)
-                : launch_staged_t<int32_t, false>(tile, items, work, kind, b, grid, st);
+        return pred ? launch_staged_t<float, true>(tile, items, work, kind, b, grid, ahead, st)
+                    : launch_staged_t<float, false>(tile, items, work, kind, b, grid, ahead, st);
+    return pred ? launch_staged_t<int32_t, true>(tile, items, work, kind, b, grid, ahead, st)
+                : launch_staged_t<int32_t, false>(tile, items, work, kind, b, grid, ahead, st);
 }
 
 int status_of(hipError_t e) {
@@ -713,6 +705,7 @@ struct StagedLaunch {
     // groups on nothing in each other: the tile size, or minus it for the
     // one-launch closures of a tile group's single-block graphs
     int group;
+    bool ahead;  // closures that work ahead (closes_ahead)
 };
 
 struct fw_batch_plan_s {
@@ -788,6 +781,28 @@ void xcd_group(std::vector<StagedWork> &work, int64_t first, int groups) {
             if (pos[x] < lists[x].size()) work[(size_t)out++] = lists[x][pos[x]++];
 }
 
+// Which form a 128-wide diagonal launch without predecessors takes; v: the
+// vertices of its tiles, descending.  The form that closes ahead has a CU to
+// itself (registers) and half the chain per vertex in fp32, 0.63 of it in int32;
+// of the 256-thread form several share a CU.
+//   - Up to a tile per CU it always ends sooner: 64 to 256 fp32 graphs of 128
+//     vertices as one captured launch 36-38 us, in 256 threads 54-56 (in 1024
+//     threads with two plain steps a barrier 45-48).
+//   - Up to two, a CU's second tile follows its first, and costs as much as 50
+//     more vertices besides: worth it where the tiles differ in size (fp32 graphs
+//     of 65 to 128: 288 45 us against 57, 448 54 against 58), not where they are
+//     alike (288 of 65 to 80: 42 against 40; 320 of 128: 67 against 62).
+//   - Beyond, the chip is full: 1024 of 65 to 128 104 us against 77.
+constexpr int kCus = 256;
+bool closes_ahead(int dtype, const std::vector<int> &v) {
+    if (v.size() <= kCus) return true;
+    if (v.size() > 2 * kCus) return false;
+    int longest = 0;  // of two tiles on one CU, the larger ones taken first
+    for (size_t j = kCus; j < v.size(); ++j)
+        longest = std::max(longest, v[2 * kCus - 1 - j] + v[j]);
+    return (longest + 50) * (dtype == FW_F32 ? 1.0 : 1.25) < 2 * v[0];
+}
+
 // Host half of a batch plan: the sorted descriptor table (header + items),
 // the stage-batched launches and their work table.  No device memory.
 struct HostPlan {
@@ -855,9 +870,16 @@ int build_host_plan(void *const *d, const int64_t *n, const int64_t *ld, int64_t
     for (int64_t g = 0; g < n_staged; ++g) groups[items[(size_t)g].tile].push_back((int32_t)g);
     auto add_launch = [&](int kind, int tile, int b, int64_t first, int group = 0) {
         if ((int64_t)work.size() > first) {
+            bool ahead = false;
+            if (kind == kStagedDiag && tile == 128 && !any_pred) {
+                std::vector<int> v;
+                for (int64_t e = first; e < (int64_t)work.size(); ++e)
+                    v.push_back(std::min(items[(size_t)work[(size_t)e].item].n - b * 128, 128));
+                ahead = closes_ahead(dtype, v);
+            }
             if (FW_STAGED_XCD_GROUPS > 1) xcd_group(work, first, FW_STAGED_XCD_GROUPS);
             hp.staged.push_back(
-                {kind, tile, b, first, (int64_t)work.size() - first, group ? group : tile});
+                {kind, tile, b, first, (int64_t)work.size() - first, group ? group : tile, ahead});
         }
     };
     for (auto &kv : groups) {
@@ -1015,7 +1037,7 @@ int enqueue_plan(fw_batch_plan_s *pl, hipStream_t st, bool untimed, hipStream_t 
         for (const StagedLaunch &l : pl->staged) {
             if (split && (pass == 0) == (l.group == main)) continue;
             e = launch_staged(pl->dtype, pl->pred, l.tile, items, pl->work + l.offset, l.kind,
-                              l.b, (unsigned)l.count, pass == 0 ? other : st);
+                              l.b, (unsigned)l.count, l.ahead, pass == 0 ? other : st);
             if (e != hipSuccess) return status_of(e);
             if (pass == 1 && (e = do_fork()) != hipSuccess) return status_of(e);
         }

@@ -43,6 +43,32 @@ def test_bits_of_a_solve_alone(n, pad, count):
         assert (whole[:, n:] == 7).all()
 
 
+@pytest.mark.parametrize("dtype", [np.float32, np.int32])
+@pytest.mark.parametrize("count", [300, 512, 513])
+def test_sizes_that_differ(count, dtype):
+    """Between a tile per CU and two, the sizes decide the form: here they differ
+    (65 to 200), so 300 and 512 graphs' closures work ahead, in rounds, in both
+    stages, and 513 graphs' do not."""
+    sizes = [round(65 * (200 / 65) ** ((g * 0.6180339887498949) % 1)) for g in range(count)]
+    code = "f32" if dtype == np.float32 else "i32"
+    alone, batch = {}, []
+    try:
+        fw.plan_set(code, 65, 200, 128)
+        for n in sorted(set(sizes)):
+            w = gen.dense_graph(n, 0.3, 1, 50, seed=n, dtype=dtype)
+            if dtype == np.float32:
+                w += np.random.default_rng(n).random((n, n), dtype=np.float32)
+                np.fill_diagonal(w, 0)
+            src = torch.from_numpy(w).cuda()
+            alone[n] = (src, fw.fw_apsp_plan(src.clone(), 128)[0])
+        batch = [alone[n][0].clone() for n in sizes]
+        fw.fw_apsp_batched(batch)
+    finally:
+        fw.plan_reset()
+    for n, d in zip(sizes, batch):
+        assert torch.equal(d.view(torch.int32), alone[n][1].view(torch.int32)), n
+
+
 @pytest.mark.parametrize("tile", [32, 64, 128])
 @pytest.mark.parametrize("pad", [0, 1])
 @pytest.mark.parametrize("dtype", [np.float32, np.int32])
