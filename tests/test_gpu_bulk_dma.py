@@ -1,7 +1,6 @@
-"""Bulk phase at tile 128 over many tiles: the direct global->LDS copy kernel
-(full tiles, 16-byte aligned rows), the edge-tile launch of a partial last
-block, and the register-staged kernel for unaligned rows, all bit-exact
-against the oracle."""
+"""Bulk phase at tile 128 over many tiles: the direct global->LDS copy kernel with
+16-byte copies (16-byte aligned rows) and 4-byte ones (other rows, and the tiles
+of a partial last block), all bit-exact against the oracle."""
 import numpy as np
 import pytest
 import torch
@@ -36,7 +35,7 @@ def run(W, ld_extra, fill, semiring="minplus"):
     return d.cpu().numpy()
 
 
-# 16-byte aligned rows (ld % 4 == 0) take the copy kernel; ld_extra 3 does not
+# 16-byte aligned rows (ld % 4 == 0) take the 16-byte copies, ld_extra 3 the 4-byte ones
 @pytest.mark.parametrize("ld_extra", [0, 4, 3])
 @pytest.mark.parametrize("dtype", ["f32", "i32"])
 @pytest.mark.parametrize("n", [256, 384, 640, 700, 1000, 1151])

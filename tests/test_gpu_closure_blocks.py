@@ -1,4 +1,4 @@
-"""The diagonal closure in 16-vertex sub-blocks and the 64-wide tile staged
+"""The diagonal closure in 8-vertex sub-blocks and the 64-wide tile staged
 whole: sub-block remainders, the smallest tiles, both closing forms, the two
 thread counts of the 64-wide launches, unaligned rows, every arithmetic.
 Whole results against the oracle, bit for bit (integer weights)."""
@@ -23,8 +23,8 @@ def _on_gpu(w, pad):
 
 
 # 2, 15 .. 17, 31 .. 33, 47 .. 49: sub-block remainders of one tile; 63 .. 65,
-# 127 .. 129: one tile and the first of a second; 1536, 1537 and 1601: 23^2 and
-# 24^2 = 576 bulk tiles (two halves of k per tile) and 25^2 (one)
+# 127 .. 129: one tile and the first of a second; 1536, 1537 and 1601: 23^2, 24^2
+# and 25^2 bulk tiles (two halves of k per tile)
 @pytest.mark.parametrize("n", [2, 15, 16, 17, 31, 32, 33, 47, 48, 49, 63, 64, 65, 112, 113, 127,
                                128, 129, 1536, 1537, 1601])
 @pytest.mark.parametrize("dtype", [np.float32, np.int32])
